@@ -34,7 +34,7 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0   # dense BF16 / FP16 MFMA
 def _pm_sources_digest(dtype: str = "f32") -> str:
     """Digest of the sources of the partial-MTTKRP kernels for one tensor dtype."""
     h = hashlib.sha256()
-    kern = ("pm_kernels.hip",) if dtype == "f32" else ("pm16_body.hpp", "pm16_kernels.hip")
+    kern = ("pm_kernels.hip", "pm_f32_body.hpp") if dtype == "f32" else ("pm16_body.hpp", "pm16_kernels.hip")
     for f in ("nncp_internal.hpp", "pm_common.hpp", *kern, "pm_plan.hip"):
         p = os.path.join(ROOT, "paper_1806_07985_amd", "csrc", f)
         if os.path.exists(p):

@@ -11,9 +11,9 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB_DIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIB_DIR, "libnncp.so")
-SOURCES = ["pm_plan.hip", "pm_kernels.hip", "pm16_kernels.hip", "pm16_bf16.hip", "pm16_f16.hip", "pm16_bf16_mt.hip",
-           "pm16_f16_mt.hip", "small_kernels.hip",
-           "driver.hip", "server.cpp", "noalloc.hip"]
+SOURCES = ["pm_f32_left.hip", "pm_f32_right.hip", "pm_f32_left_mt.hip", "pm_f32_right_mt.hip", "pm16_bf16.hip",
+           "pm16_f16.hip", "pm16_bf16_mt.hip", "pm16_f16_mt.hip", "pm_kernels.hip", "pm16_kernels.hip",
+           "small_kernels.hip", "pm_plan.hip", "driver.hip", "server.cpp", "noalloc.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17",

@@ -137,6 +137,8 @@ const void* pm16_kernel_form(int side, int nb, int j1, int fast, bool batch);
 // padded i1, and on the left side no row group straddling a column end): the
 // kernels then skip the per-step check.
 bool pm_f32_fast(int side, int64_t IL, int I1, int nb, bool xs = false);
+// The lane offsets of the range-checked loads (pm_f32_body.hpp, LD_BUF) fit 31 bits.
+bool pm_f32_buf(int side, int64_t IL, int nb);
 bool pm16_fast(int side, int64_t IL, int I1, int nb);
 template <int DT>
 const void* pm16_pack_kernel(bool batch);
@@ -258,7 +260,7 @@ struct PackArgs {        // term pack of the first contracted factor (16-bit ten
 };
 
 enum KKind : int {
-  K_PM_F32 = 1,     // variant: xs*100000 + wide*10000 + side*1000 + nb*100 + mt*10 + fast
+  K_PM_F32 = 1,     // variant: xs*100000 + wide*10000 + side*1000 + nb*100 + mt*10 + load form
   K_PM_16 = 2,      // variant: j1*100000 + (dtype == BF16)*10000 + side*1000 + nb*100 + mt*10 + fast
   K_PACK16 = 3,     // variant: dtype == BF16
   K_PM_REDUCE = 4,  // variant: t_f64

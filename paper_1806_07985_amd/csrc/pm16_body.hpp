@@ -111,14 +111,9 @@ __device__ __forceinline__ void pack_body(const PackArgs& pa, int r) {
 }
 
 // Per-(j, column) factors of a work-group's j block: Krest(j0 + jj, col0 + r)
-// times the column's 1/lambda product times the pack scale, in FP32: from the
-// launch's FP64 scale table when there is one (the product and the rounding to
-// FP32 are then done here, as pm_fill_scales does them), else computed here.
+// times the column's 1/lambda product (the launch's FP64 scale table) times the
+// pack scale, rounded to FP32.
 __device__ __forceinline__ void scales(const PmArgs& a, float* sc, int RP, int64_t j0, int jn) {
-  if (!a.sctab) {
-    pm_fill_scales<float>(a, sc, RP, j0, jn, a.hscale);
-    return;
-  }
   typedef double d2 __attribute__((ext_vector_type(2)));
   const d2* src = (const d2*)(a.sctab + j0 * RP);
   const int total = jn * RP / 2;  // RP is a multiple of 16

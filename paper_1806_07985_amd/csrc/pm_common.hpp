@@ -61,94 +61,79 @@ __device__ __forceinline__ double krp_scale_entry(const KrpDesc& krp, uint32_t j
   return p;
 }
 
-// Fill sc[jj * RP + r] (jj < jn, r < RP) with the Khatri-Rao scales of columns
-// col0 + r (times extra[r] when given); 0 for r >= R. Four entries per thread
-// per round trip.
-template <typename T>
-__device__ __forceinline__ void pm_fill_scales(const PmArgs& a, T* sc, int RP, int64_t j0, int jn,
-                                               const float* extra) {
-  const int total = jn * RP;
-  constexpr int CH = 4;
-  for (int e0 = threadIdx.x; e0 < total; e0 += NT * CH) {
-    double v[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int e = e0 + NT * c;
-      const int ec = e < total ? e : 0;
-      const int jj = ec / RP, r = ec - jj * RP;
-      const int rc = r < a.R ? r : 0;
-      v[c] = krp_scale_entry(a.krp, (uint32_t)(j0 + jj), a.col0 + rc);
-      if (extra) v[c] *= (double)extra[rc];
-      if (r >= a.R) v[c] = 0.0;
-    }
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const int e = e0 + NT * c;
-      if (e < total) sc[e] = (T)v[c];
-    }
-  }
+// Buffer loads: a wave-uniform resource starts at `p` and holds `rem` elements of
+// ESZ bytes; dwords at or past its end read zero (checked dword by dword), and a
+// lane whose byte offset is kBufNone reads zero without touching memory. Offsets
+// are below 2^31. Element-aligned addresses are fine (unaligned access mode).
+constexpr int kBufWord3 = 0x00020000;     // buffer resource word 3: raw 32-bit data
+constexpr int kBufNt = 2;                 // buffer load cache policy: nontemporal
+constexpr uint32_t kBufNone = 0x80000000u;
+template <int ESZ>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, int64_t rem) {
+  const int n = rem <= 0 ? 0 : (rem >= (int64_t)(0x7ffffffc / ESZ) ? 0x7ffffffc : (int)(rem * ESZ));
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, n, kBufWord3);
 }
 
 // The FP32 kernels' LDS copy of an i1 block of the first contracted factor:
 // hs[r * hp + i] = H_1(i1_0 + i, col0 + r), zero for i1 >= I1 and r >= R. A work
-// item is four consecutive rows of one column (one element-aligned 16-byte
-// load, element loads where the four straddle I1; hp, i1n and i1_0 are
-// multiples of four, so the LDS store is one aligned 16-byte write); eight
-// items per thread per round trip, all loads issued before any is stored.
+// item is four consecutive rows of one column (one 16-byte range-checked load:
+// no branch, so all the loads of a round are in flight together; hp, i1n and
+// i1_0 are multiples of four, so the LDS store is one aligned 16-byte write);
+// eight items per thread per round trip. A factor too long for 31-bit offsets
+// is read element by element.
 __device__ __forceinline__ void pm_stage_h1(const PmArgs& a, float* hs, int hp, int RP, int i1_0, int i1n) {
-  const float* f0 = a.krp.f[0];
+  const float* f0 = a.krp.f[0] + (int64_t)a.I1 * a.col0 + i1_0;
+  const int ilim = a.I1 - i1_0;  // real rows left (may exceed i1n)
+  if ((int64_t)a.I1 * RP >= (int64_t)1 << 28) {
+    for (int e = threadIdx.x; e < RP * i1n; e += NT) {
+      const int r = e / i1n, i = e - r * i1n;
+      hs[r * hp + i] = (r < a.R && i < ilim) ? f0[(int64_t)a.I1 * r + i] : 0.f;
+    }
+    return;
+  }
+  const __amdgpu_buffer_rsrc_t rs = buf_rsrc<4>(f0, (int64_t)a.I1 * a.R - i1_0);
   const int q = i1n >> 2;  // items per column
   const int total = RP * q;
   constexpr int CH = 8;
   for (int e0 = threadIdx.x; e0 < total; e0 += NT * CH) {
     f4 v[CH];
-    int dst[CH];
+    int dst[CH], left[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int e = e0 + NT * c;
       const int r = e / q, i = 4 * (e - r * q);
-      const int i1 = i1_0 + i;
-      const bool colok = e < total && r < a.R;
-      const float* src = f0 + (int64_t)a.I1 * (a.col0 + (colok ? r : 0));
-      f4 x = {0.f, 0.f, 0.f, 0.f};
-      if (colok && i1 + 4 <= a.I1) {
-        x = *(const f32v<4>*)(src + i1);
-      } else if (colok) {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = (i1 + u < a.I1) ? src[i1 + u] : 0.f;
-      }
-      v[c] = x;
+      left[c] = ilim - i;
+      const uint32_t off = (e < total && r < a.R && left[c] > 0) ? (uint32_t)(a.I1 * r + i) * 4u : kBufNone;
+      v[c] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
       dst[c] = e < total ? r * hp + i : -1;
     }
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
+    for (int c = 0; c < CH; ++c) {
+#pragma unroll
+      for (int u = 1; u < 4; ++u) v[c][u] = u < left[c] ? v[c][u] : 0.f;  // rows past I1: the next column's
       if (dst[c] >= 0) *(f4*)&hs[dst[c]] = v[c];
+    }
   }
 }
 
 // LDS prologue of the FP32 kernels: the first i1 block of H_1 and the
 // per-(j, column) Khatri-Rao scales sc[jj * RP + r] of the group's j block,
-// copied from the launch's scale table when there is one (a contiguous run of
-// jn * RP doubles; 16-byte loads, all issued before any is stored), else
-// computed here.
+// copied from the launch's scale table (a contiguous run of jn * RP doubles;
+// 16-byte loads, all issued before any is stored).
 __device__ __forceinline__ void pm_prologue(const PmArgs& a, float* hs, int hp, double* sc, int RP, int i1_0,
                                             int i1n, int64_t j0, int jn) {
   pm_stage_h1(a, hs, hp, RP, i1_0, i1n);
-  if (a.sctab) {
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    const d2* src = (const d2*)(a.sctab + j0 * RP);
-    const int total = jn * RP / 2;  // RP is a multiple of 16
-    constexpr int CH = 4;
-    for (int e0 = threadIdx.x; e0 < total; e0 += NT * CH) {
-      d2 v[CH];
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const d2* src = (const d2*)(a.sctab + j0 * RP);
+  const int total = jn * RP / 2;  // RP is a multiple of 16
+  constexpr int CH = 4;
+  for (int e0 = threadIdx.x; e0 < total; e0 += NT * CH) {
+    d2 v[CH];
 #pragma unroll
-      for (int c = 0; c < CH; ++c) v[c] = src[e0 + NT * c < total ? e0 + NT * c : 0];
+    for (int c = 0; c < CH; ++c) v[c] = src[e0 + NT * c < total ? e0 + NT * c : 0];
 #pragma unroll
-      for (int c = 0; c < CH; ++c)
-        if (e0 + NT * c < total) ((d2*)sc)[e0 + NT * c] = v[c];
-    }
-  } else {
-    pm_fill_scales<double>(a, sc, RP, j0, jn, nullptr);
+    for (int c = 0; c < CH; ++c)
+      if (e0 + NT * c < total) ((d2*)sc)[e0 + NT * c] = v[c];
   }
 }
 
