@@ -53,13 +53,14 @@ typedef enum { NNCP_F32 = 0, NNCP_BF16 = 1, NNCP_F16 = 2 } nncp_dtype;
 #define NNCP_MAX_RANK 128
 #define NNCP_MAX_SWEEPS 100000
 
-/* Options; zero-initialised means: automatic split, record every fit, use a
- * HIP graph per outer iteration, no early stop. */
+/* Options; zero-initialised means: automatic split, record every fit, no early
+ * stop. */
 typedef struct nncp_options {
   int split;          /* root split s (modes 1..s | s+1..N), 1 <= s <= N-1; <= 0: minimise I_L + I_R */
   int no_record_fit;  /* nonzero: fit[] receives only the final value */
-  int no_graph;       /* nonzero: launch kernels one by one instead of replaying a HIP graph */
-  int phase_timers;   /* nonzero: time each phase with HIP events (implies no_graph) */
+  int no_graph;       /* accepted and without effect: a plan's kernels are launched one by one on its
+                         stream, which measured faster than replaying a HIP graph */
+  int phase_timers;   /* nonzero: time each phase with HIP events */
   double tol;         /* > 0: stop when |fit_k - fit_{k-1}| < tol (host check each iteration) */
   int pm_wg_kib;      /* partial MTTKRP: aim for at least this many KiB of the tensor per work-group
                          (at most one work-group per CU); <= 0: 256. Depends only on the job, never on

@@ -8,7 +8,7 @@
 //   update    -- HALS or MU on the rows of the factor (Section II-B);
 //   finalize  -- Gram, column norms lambda, the next mode's S, and after mode N
 //                the fit (Section IV-B, appendix algorithm).
-// The whole iteration is captured once into a HIP graph and replayed.
+// Its kernels are launched one by one on the plan's stream.
 //
 // During the iteration the factor buffers hold the unnormalised result of each
 // mode's last update, and lam[n] holds its column norms; every consumer scales
@@ -295,15 +295,10 @@ struct nncp_plan {
   char* ws = nullptr;
   bool own_ws = false;
   hipStream_t user_stream = nullptr;
-  hipStream_t cap_stream = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t gexec = nullptr;
-  bool use_graph = true;
   bool phase_timers = false;
   bool record_fit = true;
   double tol = 0.0;
   double phase_ms[6] = {};
-  hipEvent_t ev[2] = {nullptr, nullptr};
 
   template <typename T>
   T* at(size_t off) const { return (T*)(ws + off); }
@@ -571,40 +566,6 @@ hipError_t enqueue_iteration(nncp_plan* P, const Sink& st0, std::vector<std::pai
   return mark(-1);
 }
 
-int destroy_graph(nncp_plan* P) {
-  if (P->gexec) hipGraphExecDestroy(P->gexec);
-  if (P->graph) hipGraphDestroy(P->graph);
-  P->gexec = nullptr;
-  P->graph = nullptr;
-  return NNCP_OK;
-}
-
-// The capture stream and its events are created on first use, so plans that are
-// only ever advanced by a batch own none.
-int ensure_capture_stream(nncp_plan* P) {
-  if (!P->cap_stream && hipStreamCreateWithFlags(&P->cap_stream, hipStreamNonBlocking) != hipSuccess)
-    return NNCP_EDEVICE;
-  for (auto& e : P->ev)
-    if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return NNCP_EDEVICE;
-  return NNCP_OK;
-}
-
-int build_graph(nncp_plan* P) {
-  destroy_graph(P);
-  if (ensure_capture_stream(P) != NNCP_OK) return NNCP_EDEVICE;
-  HIPCHK(hipStreamBeginCapture(P->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = enqueue_iteration(P, sink_of(P->cap_stream), nullptr);
-  hipGraph_t g = nullptr;
-  hipError_t e2 = hipStreamEndCapture(P->cap_stream, &g);
-  if (e != hipSuccess || e2 != hipSuccess) {
-    if (g) hipGraphDestroy(g);
-    return NNCP_EDEVICE;
-  }
-  P->graph = g;
-  HIPCHK(hipGraphInstantiate(&P->gexec, g, nullptr, nullptr, 0));
-  return NNCP_OK;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -667,7 +628,6 @@ int nncp_plan_create(nncp_plan** out, const void* X, int dtype, int N, const int
   P->X = X;
   for (int k = 0; k < N; ++k) P->H[k] = H[k];
   P->user_stream = (hipStream_t)stream;
-  P->use_graph = !(opt && (opt->no_graph || opt->phase_timers));
   P->phase_timers = opt && opt->phase_timers;
   P->record_fit = !(opt && opt->no_record_fit);
   P->tol = opt ? opt->tol : 0.0;
@@ -783,7 +743,6 @@ int nncp_autotune_split(const void* X, int dtype, int N, const int64_t* dims, in
   if (!X || !H || !dims || !best_split || reps < 1 || N < 2 || N > kMaxModes) return NNCP_EINVAL;
   nncp_options o{};
   if (opt) o = *opt;
-  o.no_graph = 1;  // no iteration is run: nothing to capture
   int best = 0, st_any = NNCP_ENOMEM;
   double best_ms = 0.0;
   for (int s = 1; s < N; ++s) {
@@ -842,7 +801,6 @@ int nncp_autotune_tree(const void* X, int dtype, int N, const int64_t* dims, int
   }
   nncp_options o{};
   if (opt) o = *opt;
-  o.no_graph = 1;  // no iteration is run: nothing to capture
   o.no_tree = 0;
   int st_any = NNCP_ENOMEM;
   double best_ms = 0.0;
@@ -882,10 +840,6 @@ int nncp_plan_set_stream(nncp_plan* P, void* stream) {
 
 int nncp_plan_destroy(nncp_plan* P) {
   if (!P) return NNCP_EINVAL;
-  destroy_graph(P);
-  if (P->cap_stream) hipStreamDestroy(P->cap_stream);
-  for (auto& e : P->ev)
-    if (e) hipEventDestroy(e);
   if (P->own_ws && P->ws) hipFree(P->ws);
   delete P;
   return NNCP_OK;
@@ -903,17 +857,7 @@ int nncp_plan_run(nncp_plan* P, int iters, double* fit, int* iters_done) {
     int chunk = std::min(iters - done, kFitCap);
     if (P->tol > 0) chunk = 1;
     if (fill_u32_launch((unsigned*)P->iter(), 1, 0u, us) != hipSuccess) return NNCP_EDEVICE;
-    if (P->use_graph) {
-      if (!P->gexec) {
-        int r = build_graph(P);
-        if (r != NNCP_OK) return r;
-      }
-      HIPCHK(hipEventRecord(P->ev[0], us));
-      HIPCHK(hipStreamWaitEvent(P->cap_stream, P->ev[0], 0));
-      for (int i = 0; i < chunk; ++i) HIPCHK(hipGraphLaunch(P->gexec, P->cap_stream));
-      HIPCHK(hipEventRecord(P->ev[1], P->cap_stream));
-      HIPCHK(hipStreamWaitEvent(us, P->ev[1], 0));
-    } else if (P->phase_timers) {
+    if (P->phase_timers) {
       for (int i = 0; i < chunk; ++i) {
         std::vector<std::pair<int, hipEvent_t>> marks;
         hipError_t e = enqueue_iteration(P, sink_of(us), &marks);
@@ -933,6 +877,10 @@ int nncp_plan_run(nncp_plan* P, int iters, double* fit, int* iters_done) {
         if (e != hipSuccess) return NNCP_EDEVICE;
       }
     } else {
+      // Plain launches: the stream keeps ahead of the device, and a kernel that
+      // waits for the one before it starts sooner than a node of a replayed
+      // graph (per iteration 14 launches at 137x201x90 R = 16: 117 us as a graph,
+      // 104 so; 128^4 R = 32 0.466 -> 0.437 ms; no graph to build either).
       for (int i = 0; i < chunk; ++i)
         if (enqueue_iteration(P, sink_of(us), nullptr) != hipSuccess) return NNCP_EDEVICE;
     }
