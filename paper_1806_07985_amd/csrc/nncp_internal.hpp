@@ -346,12 +346,65 @@ const void* small_batch_kernel_ptr(int kind, int variant);
 const void* fin_batch_kernel_ptr();
 size_t fin_batch_max_lds();
 
+// A pointer read from a record in device memory, marked as global: without this
+// the compiler takes it for one that may point at LDS, and every access through
+// it is a flat instruction that waits on the LDS counter too.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+__device__ __forceinline__ void globalize(KrpDesc& k) {
+#pragma unroll
+  for (int m = 0; m < kMaxModes; ++m) k.f[m] = as_global(k.f[m]);
+  k.lam = as_global(k.lam);
+}
+__device__ __forceinline__ void globalize(PmArgs& a) {
+  globalize(a.krp);
+  a.X = as_global((const char*)a.X);
+  a.T = as_global((char*)a.T);
+  a.partial = as_global(a.partial);
+  a.zeros = as_global((const char*)a.zeros);
+  a.hpack = as_global(a.hpack);
+  a.hscale = as_global(a.hscale);
+  a.sctab = as_global(a.sctab);
+}
+__device__ __forceinline__ void globalize(UpdateArgs& a) {
+  a.M = as_global((const char*)a.M);
+  a.W = as_global(a.W);
+  a.S = as_global(a.S);
+  a.lam_model = as_global(a.lam_model);
+  a.lam_self = as_global(a.lam_self);
+  a.W64 = as_global(a.W64);
+}
+__device__ __forceinline__ void globalize(FinalizeArgs& a) {
+  a.W = as_global(a.W);
+  a.M = as_global((const char*)a.M);
+  a.G = as_global(a.G);
+  a.lam = as_global(a.lam);
+  a.lam_model = as_global(a.lam_model);
+  a.S = as_global(a.S);
+  a.alpha = as_global(a.alpha);
+  a.fit_out = as_global(a.fit_out);
+  a.iter_counter = as_global(a.iter_counter);
+  a.gram_raw = as_global(a.gram_raw);
+  a.partial = as_global(a.partial);
+}
+__device__ __forceinline__ void globalize(ReduceArgs& a) {
+  a.part = as_global(a.part);
+  a.T = as_global((char*)a.T);
+}
+__device__ __forceinline__ void globalize(PackArgs& a) {
+  a.H1 = as_global(a.H1);
+  a.pack = as_global(a.pack);
+  a.hscale = as_global(a.hscale);
+}
+
 // Column scale of a Khatri-Rao operand, prod_j 1/lam[mode_j][r] (device code).
 __device__ __forceinline__ double krp_colscale(const KrpDesc& k, int r) {
   double s = 1.0;
   if (k.lam) {
     for (int j = 0; j < k.nm; ++j) {
-      double l = k.lam[(int64_t)k.mode[j] * k.lam_ld + r];
+      double l = as_global(k.lam)[(int64_t)k.mode[j] * k.lam_ld + r];
       s = (l > 0.0) ? s / l : 0.0;
     }
   }

@@ -663,13 +663,7 @@ template <int DT, int SIDE, int NB, bool J1, bool FAST, bool MT>
 __global__ __launch_bounds__(NT, 1) void pm16_kernel_items(const BItem* __restrict__ items,
                                                            const int* __restrict__ grp,
                                                            const KOp* __restrict__ ops) {
-  const int off = grp[0], n = grp[1];
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const BItem it = items[off + i];
-    const KOp& op = ops[it.op];
-    body<DT, SIDE, NB, J1, FAST, MT, false>(op.u.pm, it.bx, it.by);
-    __syncthreads();  // LDS is reused by the next item
-  }
+  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { body<DT, SIDE, NB, J1, FAST, MT, false>(a, bx, by); });
 }
 
 template <int DT>
@@ -682,7 +676,9 @@ __global__ __launch_bounds__(256) void pack_kernel_items(const BItem* __restrict
   const int off = grp[0], n = grp[1];
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const BItem it = items[off + i];
-    pack_body<DT>(ops[it.op].u.pk, it.bx);
+    PackArgs pa = ops[it.op].u.pk;
+    globalize(pa);
+    pack_body<DT>(pa, it.bx);
     __syncthreads();
   }
 }

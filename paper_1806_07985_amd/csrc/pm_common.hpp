@@ -201,6 +201,50 @@ __device__ __forceinline__ void pm_store_rows(const PmArgs& a, bool direct, int6
   }
 }
 
+// The loop of a batched partial-MTTKRP kernel over its items: body(args, bx, by)
+// for items grp[0] + b, grp[0] + b + gridDim.x, ... below grp[0] + grp[1] of
+// work-group b. An item's arguments are two dependent round trips away (item,
+// then record), and a group runs one item after another, so the record of the
+// next item is fetched while this one runs (one dword per lane, two registers)
+// and then spread to scalar registers.
+template <typename F>
+__device__ __forceinline__ void pm_walk_items(const BItem* __restrict__ items, const int* __restrict__ grp,
+                                              const KOp* __restrict__ ops, F&& body) {
+  constexpr int ND = sizeof(PmArgs) / 4;
+  static_assert(sizeof(PmArgs) % 4 == 0 && ND > 64 && ND <= 128, "two dwords per lane");
+  const int n = grp[1], lane = threadIdx.x & 63;
+  const BItem* it = items + grp[0];
+  int i = blockIdx.x;
+  if (i >= n) return;
+  auto fetch = [&](int op, uint32_t (&v)[2]) {
+    const uint32_t* p = (const uint32_t*)&ops[op].u.pm;
+    v[0] = p[lane];
+    v[1] = p[64 + lane < ND ? 64 + lane : ND - 1];
+  };
+  BItem cur = it[i];
+  uint32_t v[2];
+  fetch(cur.op, v);
+  BItem next = it[i + (int)gridDim.x < n ? i + (int)gridDim.x : i];
+  for (;;) {
+    uint32_t w[ND];
+#pragma unroll
+    for (int k = 0; k < ND; ++k) w[k] = __builtin_amdgcn_readlane(v[k >> 6], k & 63);
+    PmArgs a;
+    __builtin_memcpy(&a, w, sizeof(a));
+    globalize(a);
+    const int bx = cur.bx, by = cur.by;
+    i += gridDim.x;
+    if (i < n) {
+      cur = next;
+      fetch(cur.op, v);
+      next = it[i + (int)gridDim.x < n ? i + (int)gridDim.x : i];
+    }
+    body(a, bx, by);
+    if (i >= n) break;
+    __syncthreads();  // LDS is reused by the next item
+  }
+}
+
 // Split of a flat step range [0, n) into WK contiguous parts.
 __device__ __forceinline__ void wave_range(int n, int wk, int WK, int* b, int* e) {
   const int per = (n + WK - 1) / WK;

@@ -541,11 +541,14 @@ __device__ __forceinline__ void pm_right_f32_body(const PmArgs& a, int bx, int b
 // launches stream at once, and with the hint the caches dropped lines (or line
 // halves) that the next k-step still needed (256-job batch: 11.2 -> 9.0 GB
 // fetched per tick, 3.24 -> 2.56 ms; the 128^4 left node alone is 0.18 ms with
-// the hint, 0.20 without).
+// the hint, 0.20 without). A batched right node keeps two k-steps in flight
+// instead of three: its lanes' 128-byte runs start anywhere in a cache line, so a
+// line is needed by two steps, and with three the lines in flight of a die's 32
+// CUs (8 MB) pass its L2 (256-job tick 2.52 -> 2.48 ms).
 template <int SIDE, int NB, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void pm_f32_body(const PmArgs& a, int bx, int by) {
   if constexpr (SIDE == 0) pm_left_f32_body<NB, left_pf(NB), LD, MT, NTL>(a, bx, by);
-  else pm_right_f32_body<NB, right_pf(NB), LD, MT, NTL>(a, bx, by);
+  else pm_right_f32_body<NB, NTL ? right_pf(NB) : 2, LD, MT, NTL>(a, bx, by);  // (batched: two steps in flight)
 }
 template <int SIDE, int NB, int LD, bool MT>
 __global__ __launch_bounds__(NT, 2) void pm_f32(PmArgs a) {
@@ -558,13 +561,7 @@ __global__ __launch_bounds__(NT, 2) void pm_f32(PmArgs a) {
 template <int SIDE, int NB, int LD, bool MT>
 __global__ __launch_bounds__(NT, 2) void pm_f32_items(const BItem* __restrict__ items, const int* __restrict__ grp,
                                                       const KOp* __restrict__ ops) {
-  const int off = grp[0], n = grp[1];
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const BItem it = items[off + i];
-    const KOp& op = ops[it.op];
-    pm_f32_body<SIDE, NB, LD, MT, false>(op.u.pm, it.bx, it.by);
-    __syncthreads();  // LDS is reused by the next item
-  }
+  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { pm_f32_body<SIDE, NB, LD, MT, false>(a, bx, by); });
 }
 
 template <int SIDE, int LD, bool MT>

@@ -303,13 +303,7 @@ __global__ __launch_bounds__(NT, 2) void pm_f32_xs(PmArgs a) {
 template <int NB, bool MT>
 __global__ __launch_bounds__(NT, 2) void pm_f32_xs_items(const BItem* __restrict__ items, const int* __restrict__ grp,
                                                          const KOp* __restrict__ ops) {
-  const int off = grp[0], n = grp[1];
-  for (int i = blockIdx.x; i < n; i += gridDim.x) {
-    const BItem it = items[off + i];
-    const KOp& op = ops[it.op];
-    pm_right_f32_xs_body<NB, xs_pf(NB), MT>(op.u.pm, it.bx, it.by);
-    __syncthreads();  // LDS is reused by the next item
-  }
+  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { pm_right_f32_xs_body<NB, xs_pf(NB), MT>(a, bx, by); });
 }
 
 // The scale table of a launch: sctab[j * RP + r] = Krest(j, col0 + r) times
@@ -334,10 +328,12 @@ __global__ __launch_bounds__(NT) void pm_scale_table_items(const BItem* __restri
     const BItem it = items[off + i];
     const KOp& op = ops[it.op];
     const int RP = op.variant;
-    const int64_t tot = op.u.pm.J * RP;
+    PmArgs a = op.u.pm;
+    globalize(a);
+    const int64_t tot = a.J * RP;
     for (unsigned c = 0; c < op.coarse; ++c) {
       const int64_t b = (int64_t)it.bx * op.coarse + c;
-      if (b < (int64_t)op.gx) scale_table_block(op.u.pm, RP, tot, b);
+      if (b < (int64_t)op.gx) scale_table_block(a, RP, tot, b);
     }
   }
 }

@@ -29,11 +29,11 @@ __device__ __forceinline__ double to_f64<_Float16>(_Float16 v) { return (double)
 
 // Element i of a buffer that holds doubles (f64 != 0) or floats.
 __device__ __forceinline__ double ldv(const void* p, int64_t i, int f64) {
-  return f64 ? ((const double*)p)[i] : (double)((const float*)p)[i];
+  return f64 ? as_global((const double*)p)[i] : (double)as_global((const float*)p)[i];
 }
 __device__ __forceinline__ void stv(void* p, int64_t i, int f64, double v) {
-  if (f64) ((double*)p)[i] = v;
-  else ((float*)p)[i] = (float)v;
+  if (f64) as_global((double*)p)[i] = v;
+  else as_global((float*)p)[i] = (float)v;
 }
 
 __device__ __forceinline__ double block_sum(double v, double* sh) {
@@ -166,7 +166,7 @@ __device__ __forceinline__ void mttv_trail_body(const MttvArgs& a, int bx, int r
   const int ti = threadIdx.x & 63, ph = threadIdx.x >> 6;
   const int64_t i = (int64_t)bx * 64 + ti;
   const double scale = krp_colscale(a.krp, r);
-  const TN* Tr = (const TN*)a.T + (int64_t)r * a.Ia * a.J;
+  const TN* Tr = as_global((const TN*)a.T) + (int64_t)r * a.Ia * a.J;
   double acc = 0.0;
   for (int64_t j0 = 0; j0 < a.J; j0 += TRAIL_KCH) {
     const int cnt = (int)((a.J - j0) < TRAIL_KCH ? (a.J - j0) : TRAIL_KCH);
@@ -183,7 +183,7 @@ __device__ __forceinline__ void mttv_trail_body(const MttvArgs& a, int bx, int r
         const uint32_t q = rem / d;
         const uint32_t dig = m < a.krp.nm ? rem - q * d : 0u;
         if (m < a.krp.nm) rem = q;
-        fv[m] = a.krp.f[mm][(int64_t)dig + (int64_t)a.krp.dim[mm] * r];
+        fv[m] = as_global(a.krp.f[mm])[(int64_t)dig + (int64_t)a.krp.dim[mm] * r];
       }
       double p = scale;
 #pragma unroll
@@ -240,10 +240,10 @@ __device__ __forceinline__ void mttv_lead_body(const MttvArgs& a, int bx) {
   if (o < total) {
     r = (int)(o / a.J);
     const int64_t j = o - (int64_t)r * a.J;
-    const TN* Tc = (const TN*)a.T + a.Ia * (j + a.J * (int64_t)r);
+    const TN* Tc = as_global((const TN*)a.T) + a.Ia * (j + a.J * (int64_t)r);
     if (a.krp.nm == 1) {
       // eight products of the lane in flight, added in increasing i
-      const float* Hc = a.krp.f[0] + a.Ia * (int64_t)r;
+      const float* Hc = as_global(a.krp.f[0]) + a.Ia * (int64_t)r;
       int64_t i = p;
       for (; i + 7 * GS < a.Ia; i += 8 * GS) {
         TN t[8];
@@ -266,7 +266,7 @@ __device__ __forceinline__ void mttv_lead_body(const MttvArgs& a, int bx) {
           for (int m = 0; m < a.krp.nm; ++m) {
             const uint32_t d = (uint32_t)a.krp.dim[m];
             const uint32_t q = rem / d;
-            k *= (double)a.krp.f[m][(int64_t)(rem - q * d) + (int64_t)d * r];
+            k *= (double)as_global(a.krp.f[m])[(int64_t)(rem - q * d) + (int64_t)d * r];
             rem = q;
           }
         } else {
@@ -274,7 +274,7 @@ __device__ __forceinline__ void mttv_lead_body(const MttvArgs& a, int bx) {
           for (int m = 0; m < a.krp.nm; ++m) {
             const int64_t d = a.krp.dim[m];
             const int64_t q = rem / d;
-            k *= (double)a.krp.f[m][(rem - q * d) + d * r];
+            k *= (double)as_global(a.krp.f[m])[(rem - q * d) + d * r];
             rem = q;
           }
         }
@@ -1020,21 +1020,23 @@ template <int EP>
 __global__ __launch_bounds__(NTF) void tail1k_kernel(FinalizeArgs a) { tail1k_body<EP>(a); }
 
 __device__ __forceinline__ void fin_op(const KOp& op, int bx) {
+  FinalizeArgs a = op.u.fin;
+  globalize(a);
   switch (op.kind) {
     case K_FIN1K:
-      if (op.variant == 1) fin1k_body<1>(op.u.fin);
-      else if (op.variant == 2) fin1k_body<2>(op.u.fin);
-      else fin1k_body<4>(op.u.fin);
+      if (op.variant == 1) fin1k_body<1>(a);
+      else if (op.variant == 2) fin1k_body<2>(a);
+      else fin1k_body<4>(a);
       break;
     case K_GRAM1K:
-      if (op.variant == 1) gram1k_chunk_body<1>(op.u.fin, bx);
-      else if (op.variant == 2) gram1k_chunk_body<2>(op.u.fin, bx);
-      else gram1k_chunk_body<4>(op.u.fin, bx);
+      if (op.variant == 1) gram1k_chunk_body<1>(a, bx);
+      else if (op.variant == 2) gram1k_chunk_body<2>(a, bx);
+      else gram1k_chunk_body<4>(a, bx);
       break;
     case K_TAIL1K:
-      if (op.variant == 1) tail1k_body<1>(op.u.fin);
-      else if (op.variant == 2) tail1k_body<2>(op.u.fin);
-      else tail1k_body<4>(op.u.fin);
+      if (op.variant == 1) tail1k_body<1>(a);
+      else if (op.variant == 2) tail1k_body<2>(a);
+      else tail1k_body<4>(a);
       break;
     default: break;
   }
@@ -1081,39 +1083,49 @@ __global__ __launch_bounds__(NT) void pm_reduce_kernel(ReduceArgs ra) {
 // Persistent batched forms of the small kernels of the iteration: one kernel
 // per kind (and per register variant of the update), so that each runs at its
 // own occupancy rather than at that of the most register-hungry one.
-template <int KIND, int VAR>
-__device__ __forceinline__ void small_op(const KOp& op, int bx, int by) {
+template <int KIND, int VAR, typename A>
+__device__ __forceinline__ void small_op(const A& a, int variant, int bx, int by) {
   if constexpr (KIND == K_PM_REDUCE) {
-    if (op.variant) pm_reduce_body<double>(op.u.red, bx);
-    else pm_reduce_body<float>(op.u.red, bx);
+    if (variant) pm_reduce_body<double>(a, bx);
+    else pm_reduce_body<float>(a, bx);
   } else if constexpr (KIND == K_MTTV_TRAIL) {
-    if (op.variant) mttv_trail_body<double>(op.u.mt, bx, by);
-    else mttv_trail_body<float>(op.u.mt, bx, by);
+    if (variant) mttv_trail_body<double>(a, bx, by);
+    else mttv_trail_body<float>(a, bx, by);
   } else if constexpr (KIND == K_MTTV_LEAD) {
-    switch (op.variant) {
-      case 41: mttv_lead_body<4, double>(op.u.mt, bx); break;
-      case 40: mttv_lead_body<4, float>(op.u.mt, bx); break;
-      case 81: mttv_lead_body<8, double>(op.u.mt, bx); break;
-      case 80: mttv_lead_body<8, float>(op.u.mt, bx); break;
-      case 161: mttv_lead_body<16, double>(op.u.mt, bx); break;
-      case 160: mttv_lead_body<16, float>(op.u.mt, bx); break;
-      case 321: mttv_lead_body<32, double>(op.u.mt, bx); break;
-      case 320: mttv_lead_body<32, float>(op.u.mt, bx); break;
-      case 641: mttv_lead_body<64, double>(op.u.mt, bx); break;
-      default: mttv_lead_body<64, float>(op.u.mt, bx); break;
+    switch (variant) {
+      case 41: mttv_lead_body<4, double>(a, bx); break;
+      case 40: mttv_lead_body<4, float>(a, bx); break;
+      case 81: mttv_lead_body<8, double>(a, bx); break;
+      case 80: mttv_lead_body<8, float>(a, bx); break;
+      case 161: mttv_lead_body<16, double>(a, bx); break;
+      case 160: mttv_lead_body<16, float>(a, bx); break;
+      case 321: mttv_lead_body<32, double>(a, bx); break;
+      case 320: mttv_lead_body<32, float>(a, bx); break;
+      case 641: mttv_lead_body<64, double>(a, bx); break;
+      default: mttv_lead_body<64, float>(a, bx); break;
     }
   } else if constexpr (KIND == K_UPDATE) {
-    if constexpr (VAR <= 2) update_body<VAR>(op.u.up, bx);
-    else update_reg_body<VAR>(op.u.up, bx);
-  } else if constexpr (KIND == K_FIN_FUSED) {
-    finalize_fused_body(op.u.fin);
-  } else if constexpr (KIND == K_GRAM_CHUNKS) {
-    gram_chunks_body(op.u.fin, bx);
-  } else if constexpr (KIND == K_FIN_TAIL) {
-    finalize_tail_body(op.u.fin);
+    update_reg_body<VAR>(a, bx);
   }
 }
 
+// A small op's arguments: a copy with its pointers marked global, or, for a
+// multi-TTV, the record itself (its arrays are indexed by the mode, and a copy of
+// them would live in scratch memory; its body marks the pointers).
+template <int KIND>
+__device__ __forceinline__ decltype(auto) small_args(const KOp& op) {
+  if constexpr (KIND == K_PM_REDUCE) {
+    ReduceArgs a = op.u.red;
+    globalize(a);
+    return a;
+  } else if constexpr (KIND == K_UPDATE) {
+    UpdateArgs a = op.u.up;
+    globalize(a);
+    return a;
+  } else {
+    return (op.u.mt);
+  }
+}
 template <int KIND, int VAR>
 __global__ __launch_bounds__(NT) void small_items_kernel(const BItem* __restrict__ items, const int* __restrict__ grp,
                                                          const KOp* __restrict__ ops) {
@@ -1121,9 +1133,10 @@ __global__ __launch_bounds__(NT) void small_items_kernel(const BItem* __restrict
   for (int i = blockIdx.x; i < n; i += gridDim.x) {
     const BItem it = items[off + i];
     const KOp& op = ops[it.op];
+    decltype(auto) a = small_args<KIND>(op);
     const unsigned b0 = (unsigned)it.bx * op.coarse, b1 = min(b0 + op.coarse, op.gx);
     for (unsigned b = b0; b < b1; ++b) {
-      small_op<KIND, VAR>(op, (int)b, it.by);
+      small_op<KIND, VAR>(a, op.variant, (int)b, it.by);
       __syncthreads();  // LDS is reused by the next work-group's share
     }
   }
@@ -1326,16 +1339,11 @@ const void* small_batch_kernel_ptr(int kind, int variant) {
     case K_MTTV_LEAD: return (const void*)small_items_kernel<K_MTTV_LEAD, 0>;
     case K_UPDATE:
       switch (variant) {
-        case 1: return (const void*)small_items_kernel<K_UPDATE, 1>;
-        case 2: return (const void*)small_items_kernel<K_UPDATE, 2>;
         case 16: return (const void*)small_items_kernel<K_UPDATE, 16>;
         case 32: return (const void*)small_items_kernel<K_UPDATE, 32>;
         case 64: return (const void*)small_items_kernel<K_UPDATE, 64>;
         default: return nullptr;
       }
-    case K_FIN_FUSED: return (const void*)small_items_kernel<K_FIN_FUSED, 0>;
-    case K_GRAM_CHUNKS: return (const void*)small_items_kernel<K_GRAM_CHUNKS, 0>;
-    case K_FIN_TAIL: return (const void*)small_items_kernel<K_FIN_TAIL, 0>;
     default: return nullptr;
   }
 }
