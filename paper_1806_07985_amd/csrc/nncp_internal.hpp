@@ -132,7 +132,7 @@ int pm_16_kstep(int side);
 size_t pm_16_reduce_lds(int side, int nb, int wm);
 hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk);
 template <int DT, bool MT>
-const void* pm16_kernel_form(int side, int nb, int j1, int fast, bool batch);
+const void* pm16_kernel_form(int side, int nb, int j1, int ld, bool batch);
 // Every vector load of every k-step lies inside the tensor for this shape (no
 // padded i1, and on the left side no row group straddling a column end): the
 // kernels then skip the per-step check.
@@ -140,8 +140,9 @@ bool pm_f32_fast(int side, int64_t IL, int I1, int nb, bool xs = false);
 // The lane offsets of the range-checked loads (pm_f32_body.hpp, LD_BUF) fit 31 bits.
 bool pm_f32_buf(int side, int64_t IL, int nb);
 bool pm16_fast(int side, int64_t IL, int I1, int nb);
+bool pm16_buf(int side, int64_t IL, int nb, int j1);
 template <int DT>
-const void* pm16_pack_kernel(bool batch);
+const void* pm16_pack_kernel(bool batch, int threads);
 // Batched (work-list) forms of the partial-MTTKRP kernels, by recorded variant.
 const void* pm_f32_batch_kernel(int variant);
 const void* pm16_batch_kernel(int variant);
@@ -261,7 +262,7 @@ struct PackArgs {        // term pack of the first contracted factor (16-bit ten
 
 enum KKind : int {
   K_PM_F32 = 1,     // variant: xs*100000 + wide*10000 + side*1000 + nb*100 + mt*10 + load form
-  K_PM_16 = 2,      // variant: j1*100000 + (dtype == BF16)*10000 + side*1000 + nb*100 + mt*10 + fast
+  K_PM_16 = 2,      // variant: j1*100000 + (dtype == BF16)*10000 + side*1000 + nb*100 + mt*10 + load form
   K_PACK16 = 3,     // variant: dtype == BF16
   K_PM_REDUCE = 4,  // variant: t_f64
   K_MTTV_TRAIL = 5, // variant: t_f64

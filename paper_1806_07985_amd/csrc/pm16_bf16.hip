@@ -4,5 +4,5 @@
 
 namespace nncpk {
 template const void* pm16_kernel_form<NNCP_BF16, false>(int, int, int, int, bool);
-template const void* pm16_pack_kernel<NNCP_BF16>(bool);
+template const void* pm16_pack_kernel<NNCP_BF16>(bool, int);
 }  // namespace nncpk

@@ -24,8 +24,8 @@
 //    operand. Right side: k is contiguous, so one 16-byte load is the operand.
 //  * Loads are vector loads for any shape (element-aligned): padded i1 reads
 //    the next j's columns against zero rows of H_1, rows past the output read
-//    into the next column and feed outputs that are never stored; the one
-//    k-step that could read past the tensor's end loads element by element.
+//    into the next column and feed outputs that are never stored; reads past the
+//    tensor's end are range-checked to zero (buffer loads).
 //  * When one LDS block cannot hold all of I1 and the output is tall (the
 //    right node of a tensor whose first mode is long), a work-group walks the
 //    i1 blocks in turn and restages LDS between them, instead of splitting K
@@ -70,9 +70,9 @@ struct T16<NNCP_F16> {
 // term: t_0 = round(v), t_1 = round(v - t_0), t_2 = round(v - t_0 - t_1) (each
 // difference is exact in FP32); rows I1..I1pad-1 and columns r >= R are 0.
 // hscale[r] = 2^-e.
-template <int DT>
+template <int DT, int NTH>
 __device__ __forceinline__ void pack_body(const PackArgs& pa, int r) {
-  __shared__ float red[256];
+  __shared__ float red[NTH];
   const float* __restrict__ H1 = pa.H1;
   const int I1 = pa.I1, I1pad = pa.I1pad, R = pa.R, col0 = pa.col0, RP = pa.RP;
   unsigned short* __restrict__ pack = pa.pack;
@@ -81,10 +81,10 @@ __device__ __forceinline__ void pack_body(const PackArgs& pa, int r) {
   const float* h = H1 + (int64_t)I1 * (col0 + r);
   float mx = 0.f;
   if (live)
-    for (int i = threadIdx.x; i < I1; i += 256) mx = fmaxf(mx, fabsf(h[i]));
+    for (int i = threadIdx.x; i < I1; i += NTH) mx = fmaxf(mx, fabsf(h[i]));
   red[threadIdx.x] = mx;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = NTH / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + w]);
     __syncthreads();
   }
@@ -98,7 +98,7 @@ __device__ __forceinline__ void pack_body(const PackArgs& pa, int r) {
   }
   const float up = ldexpf(1.f, e);
   constexpr int NTM = pm16_terms(DT);
-  for (int i = threadIdx.x; i < I1pad; i += 256) {
+  for (int i = threadIdx.x; i < I1pad; i += NTH) {
     float v = (live && i < I1) ? h[i] * up : 0.f;
 #pragma unroll
     for (int t = 0; t < NTM; ++t) {
@@ -188,6 +188,30 @@ __device__ __forceinline__ void reduce_waves(float (&accf)[NACC][4], double* lds
     for (int e = 0; e < 4; ++e) accf[v][e] = (float)acc[v][e];
 }
 
+// How the tensor is loaded. LD_FAST: plain vector loads, for shapes that guarantee
+// that all of them lie inside the tensor (pm16_fast). LD_BUF: range-checked buffer
+// loads, which read zeros past the tensor's end, for shapes whose lane offsets fit
+// 31 bits (pm16_buf). The check is made per dword
+// and drops one that is half inside, so a tensor whose last element falls into
+// such a dword has it put in place when its step is computed (`put_last`).
+// LD_GEN: the rest (columns of hundreds of MB): a uniform check per step, masked
+// element loads in the steps that reach the tensor's end; their branches make the
+// compiler wait for every load in flight once per ring round.
+enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2 };
+template <int L, bool NTL>
+__device__ __forceinline__ u16v<L> buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  constexpr int aux = NTL ? kBufNt : 0;
+  if constexpr (L == 8) return __builtin_bit_cast(u16v<8>, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, aux));
+  else return __builtin_bit_cast(u16v<4>, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, aux));
+}
+// v holds elements whose d-th and later lie past the tensor: if that cut a dword
+// in half (d odd), its inside half is the tensor's last element.
+template <int L>
+__device__ __forceinline__ void put_last(u16v<L>& v, int d, unsigned short last) {
+#pragma unroll
+  for (int e = 0; e < L; e += 2) v[e] = d == e + 1 ? last : v[e];
+}
+
 // Rows per left wave = 16 * TR, columns per right wave = 16 * MC.
 constexpr int left_tr16(int nb) { return nb >= 4 ? 4 : 8; }
 constexpr int right_mc16(int nb) { return 4; }
@@ -202,7 +226,7 @@ constexpr int right_pf16(int nb) { return 3; }
 // TR*li .. TR*li+TR-1 of the 8 columns i1 = base + 8*lq + e; MFMA tile tt takes
 // row TR*li + tt of those 8 loads as its 8-k operand.
 // ----------------------------------------------------------------------------
-template <int DT, int NB, bool FAST, bool MT, bool NTL>
+template <int DT, int NB, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
   constexpr int RP = NB * 16;
   constexpr int TR = left_tr16(NB);
@@ -260,6 +284,17 @@ __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
   // (row group start <= Mtot - 1, TR rows, in the step's last column): all of
   // them lie inside the tensor while Mtot * (colbase + KS) <= vec_lim.
   const int64_t vec_lim = Mtot * Ktot - (TR - 1);
+  // LD_BUF: the resource of a step starts at the wave's first row of the step's
+  // first column; lane byte offsets (rows past the output: none)
+  const int64_t IX = Mtot * Ktot;
+  uint32_t voff[8];
+  auto set_voff = [&]() {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      voff[e] = m < Mtot ? (uint32_t)((Mtot * (int64_t)(8 * lq + e) + TR * li) * 2) : kBufNone;
+  };
+  if constexpr (LD == LD_BUF) set_voff();
+  const unsigned short xlast = LD == LD_BUF ? X[IX - 1] : 0;
 
   const int jrot = (WK == 1 && jn > 1) ? (int)(((unsigned)bx * 5u) % (unsigned)jn) : 0;
   int jcntL = sb / S1, tileL = 0;
@@ -268,7 +303,12 @@ __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
   auto load = [&](vT (&A)[8]) {
     const int64_t colbase = (int64_t)a.I1 * (j0 + jl) + i1_0 + KS * tl;
     const unsigned short* base = X + Mtot * (colbase + 8 * lq);
-    if (FAST || Mtot * (colbase + KS) <= vec_lim) {  // uniform
+    if constexpr (LD == LD_BUF) {
+      const int64_t e0 = Mtot * colbase + (int64_t)(tile0 + tileL) * mtile + wm * WROWS;
+      const __amdgpu_buffer_rsrc_t rs = buf_rsrc<2>(X + e0, IX - e0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) A[e] = buf_load16<TR, NTL>(rs, voff[e]);
+    } else if (LD == LD_FAST || Mtot * (colbase + KS) <= vec_lim) {  // uniform
 #pragma unroll
       for (int e = 0; e < 8; ++e) A[e] = tload<NTL>((const vT*)(base + Mtot * e + mload));
     } else {
@@ -298,6 +338,7 @@ __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
         if (++tileL == ntile) tileL = 0;
         m = (int64_t)(tile0 + tileL) * mtile + wm * WROWS + TR * li;
         mload = m < Mtot ? m : 0;
+        if constexpr (LD == LD_BUF) set_voff();
       }
     }
   };
@@ -322,8 +363,15 @@ __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) c32[tt][nb] = f4{0.f, 0.f, 0.f, 0.f};
   int jc = jl, tc = tl, jcntC = jcntL, tileC = 0, left = se - sb;
-  auto compute = [&](const vT (&A)[8]) {
+  auto compute = [&](vT (&A)[8]) {
     const int kk = KS * tc + 8 * lq;
+    if (LD == LD_BUF && (Mtot & 1) && tc + 1 == S1 && j0 + jc + 1 == a.J && i1_0 + i1n == a.I1pad) {
+      // the step with the tensor's last column
+      const int64_t mc = (int64_t)(tile0 + tileC) * mtile + wm * WROWS + TR * li;
+      const int d = mc < Mtot && Mtot - mc < TR ? (int)(Mtot - mc) : 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) put_last<TR>(A[e], kk + e + 1 == ilim ? d : 0, xlast);
+    }
     u4 B[NTM][NB];
 #pragma unroll
     for (int t = 0; t < NTM; ++t)
@@ -402,7 +450,7 @@ __device__ __forceinline__ void left_body(const PmArgs& a, int bx, int by) {
 // factor per column: the MFMA sums run over all of K (FP32) and are scaled once
 // at the end, with no separate accumulators (every wave owns its columns).
 // ----------------------------------------------------------------------------
-template <int DT, int NB, bool J1, bool FAST, bool MT, bool NTL>
+template <int DT, int NB, bool J1, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   constexpr int RP = NB * 16;
   constexpr int MC = J1 ? right_mc16_j1(NB) : right_mc16(NB);
@@ -458,12 +506,22 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   // of them lie inside the tensor while lbase <= vec_lim.
   const unsigned short* colp[MC];
   int64_t vec_lim;
+  // LD_BUF: the resource of a step starts at the step's first element of the
+  // wave's first column (cwk); lane byte offsets (columns past the output: none)
+  const int64_t IX = Mtot * Ktot;
+  int64_t cwk = 0;
+  uint32_t voff[MC];
+  const unsigned short xlast = LD == LD_BUF ? X[IX - 1] : 0;
   auto set_tile = [&](int t) {
     const int64_t cw = (int64_t)(tile0 + t) * mtile + wm * 16 * MC;
+    cwk = cw * Ktot;
 #pragma unroll
     for (int g = 0; g < MC; ++g) {
       const int64_t c = cw + 16 * g + li;
-      colp[g] = X + Ktot * (c < Mtot ? c : 0) + 8 * lq;
+      if constexpr (LD == LD_BUF)
+        voff[g] = c < Mtot ? (uint32_t)(((int64_t)(16 * g + li) * Ktot + 8 * lq) * 2) : kBufNone;
+      else
+        colp[g] = X + Ktot * (c < Mtot ? c : 0) + 8 * lq;
     }
     const int64_t cmax = min(cw + 16 * MC - 1, Mtot - 1);
     vec_lim = Mtot * Ktot - Ktot * cmax - KS;  // wave-uniform
@@ -483,7 +541,13 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   auto load = [&](vT (&A)[MC][2]) {
     const int i1s = (ib0 + stL) * a.i1blk;
     const int64_t lbase = (int64_t)a.I1 * (j0 + jl) + i1s + KS * tl;
-    if (FAST || lbase <= vec_lim) {  // uniform
+    if constexpr (LD == LD_BUF) {
+      const __amdgpu_buffer_rsrc_t rs = buf_rsrc<2>(X + cwk + lbase, IX - cwk - lbase);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int g = 0; g < MC; ++g) A[g][h] = buf_load16<8, NTL>(rs, voff[g] + 64 * h);
+    } else if (LD == LD_FAST || lbase <= vec_lim) {  // uniform
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -559,8 +623,17 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
       }
   };
   int stC = 0, S1C = S1L, jc = jl, tc = tl, jcntC = jcntL, tileC = 0, left = se - sb;
-  auto compute = [&](const vT (&A)[MC][2]) {
+  auto compute = [&](vT (&A)[MC][2]) {
     const int kk = KS * tc + 8 * lq;
+    if (LD == LD_BUF && (a.I1 & 1) && tc + 1 == S1C && j0 + jc + 1 == a.J && ib0 + stC + 1 == a.n_i1blk) {
+      // the step with the end of the tensor's last column
+      const int64_t cw = (int64_t)(tile0 + tileC) * mtile + wm * 16 * MC;
+      const int d = a.I1 - (ib0 + stC) * a.i1blk - kk;
+#pragma unroll
+      for (int g = 0; g < MC; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) put_last<8>(A[g][h], cw + 16 * g + li + 1 == Mtot ? d - 32 * h : 0, xlast);
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       u4 B[NTM][NB];
@@ -643,32 +716,31 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   store_tile((int64_t)(tile0 + ntile - 1) * mtile + wm * 16 * MC);
 }
 
-// FAST: the shape guarantees that every vector load of every step lies inside
-// the tensor (pm16_fast), so the loads need no per-step check. NTL: tensor loads
-// with the streaming hint (stand-alone launches; see pm_f32_body).
-template <int DT, int SIDE, int NB, bool J1, bool FAST, bool MT, bool NTL>
+// NTL: tensor loads with the streaming hint: stand-alone left nodes whose columns
+// start on cache lines (see pm_f32_body.hpp).
+template <int DT, int SIDE, int NB, bool J1, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void body(const PmArgs& a, int bx, int by) {
-  if (SIDE == 0) left_body<DT, NB, FAST, MT, NTL>(a, bx, by);
-  else right_body<DT, NB, J1, FAST, MT, NTL>(a, bx, by);
+  if (SIDE == 0) left_body<DT, NB, LD, MT, NTL>(a, bx, by);
+  else right_body<DT, NB, J1, LD, MT, NTL>(a, bx, by);
 }
 
 // Stand-alone kernels: one work-group per (M tile, split).
-template <int DT, int SIDE, int NB, bool J1, bool FAST, bool MT>
+template <int DT, int SIDE, int NB, bool J1, int LD, bool MT>
 __global__ __launch_bounds__(NT, 1) void pm16_kernel_std(PmArgs a) {
-  body<DT, SIDE, NB, J1, FAST, MT, true>(a, blockIdx.x, blockIdx.y);
+  body<DT, SIDE, NB, J1, LD, MT, SIDE == 0 && LD == LD_FAST>(a, blockIdx.x, blockIdx.y);
 }
 // Persistent batched form: items grp[0] + b, grp[0] + b + gridDim.x, ... below
 // grp[0] + grp[1], each one (M tile, split) work-group of a recorded launch.
-template <int DT, int SIDE, int NB, bool J1, bool FAST, bool MT>
+template <int DT, int SIDE, int NB, bool J1, int LD, bool MT>
 __global__ __launch_bounds__(NT, 1) void pm16_kernel_items(const BItem* __restrict__ items,
                                                            const int* __restrict__ grp,
                                                            const KOp* __restrict__ ops) {
-  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { body<DT, SIDE, NB, J1, FAST, MT, false>(a, bx, by); });
+  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { body<DT, SIDE, NB, J1, LD, MT, false>(a, bx, by); });
 }
 
-template <int DT>
-__global__ __launch_bounds__(256) void pack_kernel_std(PackArgs pa) {
-  pack_body<DT>(pa, blockIdx.x);
+template <int DT, int NTH>
+__global__ __launch_bounds__(NTH) void pack_kernel_std(PackArgs pa) {
+  pack_body<DT, NTH>(pa, blockIdx.x);
 }
 template <int DT>
 __global__ __launch_bounds__(256) void pack_kernel_items(const BItem* __restrict__ items, const int* __restrict__ grp,
@@ -678,53 +750,59 @@ __global__ __launch_bounds__(256) void pack_kernel_items(const BItem* __restrict
     const BItem it = items[off + i];
     PackArgs pa = ops[it.op].u.pk;
     globalize(pa);
-    pack_body<DT>(pa, it.bx);
+    pack_body<DT, 256>(pa, it.bx);
     __syncthreads();
   }
 }
 
-template <int DT, int SIDE, bool J1, bool FAST, bool MT>
+template <int DT, int SIDE, bool J1, int LD, bool MT>
 const void* pick(int nb, bool batch) {
   switch (nb) {
     case 1:
-      return batch ? (const void*)pm16_kernel_items<DT, SIDE, 1, J1, FAST, MT>
-                   : (const void*)pm16_kernel_std<DT, SIDE, 1, J1, FAST, MT>;
+      return batch ? (const void*)pm16_kernel_items<DT, SIDE, 1, J1, LD, MT>
+                   : (const void*)pm16_kernel_std<DT, SIDE, 1, J1, LD, MT>;
     case 2:
-      return batch ? (const void*)pm16_kernel_items<DT, SIDE, 2, J1, FAST, MT>
-                   : (const void*)pm16_kernel_std<DT, SIDE, 2, J1, FAST, MT>;
+      return batch ? (const void*)pm16_kernel_items<DT, SIDE, 2, J1, LD, MT>
+                   : (const void*)pm16_kernel_std<DT, SIDE, 2, J1, LD, MT>;
     case 4:
       if constexpr (J1 && MT) {
         return nullptr;  // not planned: the J == 1 kernel at four column blocks has no registers to spare
       } else {
-        return batch ? (const void*)pm16_kernel_items<DT, SIDE, 4, J1, FAST, MT>
-                     : (const void*)pm16_kernel_std<DT, SIDE, 4, J1, FAST, MT>;
+        return batch ? (const void*)pm16_kernel_items<DT, SIDE, 4, J1, LD, MT>
+                     : (const void*)pm16_kernel_std<DT, SIDE, 4, J1, LD, MT>;
       }
     default: return nullptr;
   }
 }
 
-template <int DT, bool FAST, bool MT>
+template <int DT, int LD, bool MT>
 const void* pick_side(int side, int nb, int j1, bool batch) {
-  if (j1) return side == 1 ? pick<DT, 1, true, FAST, MT>(nb, batch) : nullptr;
-  return side == 0 ? pick<DT, 0, false, FAST, MT>(nb, batch) : pick<DT, 1, false, FAST, MT>(nb, batch);
+  if (j1) return side == 1 ? pick<DT, 1, true, LD, MT>(nb, batch) : nullptr;
+  return side == 0 ? pick<DT, 0, false, LD, MT>(nb, batch) : pick<DT, 1, false, LD, MT>(nb, batch);
 }
 
 template <int DT, bool MT>
-const void* pick_fast(int side, int nb, int j1, int fast, bool batch) {
-  return fast ? pick_side<DT, true, MT>(side, nb, j1, batch) : pick_side<DT, false, MT>(side, nb, j1, batch);
+const void* pick_load(int side, int nb, int j1, int ld, bool batch) {
+  switch (ld) {
+    case LD_FAST: return pick_side<DT, LD_FAST, MT>(side, nb, j1, batch);
+    case LD_BUF: return pick_side<DT, LD_BUF, MT>(side, nb, j1, batch);
+    default: return pick_side<DT, LD_GEN, MT>(side, nb, j1, batch);
+  }
 }
 
 }  // namespace pm16
 
-// Kernel of (side, column blocks, J == 1 form, unchecked loads), stand-alone or
+// Kernel of (side, column blocks, J == 1 form, load form), stand-alone or
 // batched, in the one-tile (MT false) or several-tile form.
 template <int DT, bool MT>
-const void* pm16_kernel_form(int side, int nb, int j1, int fast, bool batch) {
-  return pm16::pick_fast<DT, MT>(side, nb, j1, fast, batch);
+const void* pm16_kernel_form(int side, int nb, int j1, int ld, bool batch) {
+  return pm16::pick_load<DT, MT>(side, nb, j1, ld, batch);
 }
+// (batched, or stand-alone with 256 or 1024 threads per column)
 template <int DT>
-const void* pm16_pack_kernel(bool batch) {
-  return batch ? (const void*)pm16::pack_kernel_items<DT> : (const void*)pm16::pack_kernel_std<DT>;
+const void* pm16_pack_kernel(bool batch, int threads) {
+  if (batch) return (const void*)pm16::pack_kernel_items<DT>;
+  return threads > 256 ? (const void*)pm16::pack_kernel_std<DT, 1024> : (const void*)pm16::pack_kernel_std<DT, 256>;
 }
 
 }  // namespace nncpk

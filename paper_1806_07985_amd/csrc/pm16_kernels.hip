@@ -10,8 +10,8 @@ extern template const void* pm16_kernel_form<NNCP_BF16, false>(int, int, int, in
 extern template const void* pm16_kernel_form<NNCP_BF16, true>(int, int, int, int, bool);
 extern template const void* pm16_kernel_form<NNCP_F16, false>(int, int, int, int, bool);
 extern template const void* pm16_kernel_form<NNCP_F16, true>(int, int, int, int, bool);
-extern template const void* pm16_pack_kernel<NNCP_BF16>(bool);
-extern template const void* pm16_pack_kernel<NNCP_F16>(bool);
+extern template const void* pm16_pack_kernel<NNCP_BF16>(bool, int);
+extern template const void* pm16_pack_kernel<NNCP_F16>(bool, int);
 
 namespace {
 
@@ -19,12 +19,12 @@ constexpr int left_tr16(int nb) { return nb >= 4 ? 4 : 8; }
 constexpr int right_mc16(int nb) { return 4; }
 constexpr int right_mc16_j1(int nb) { return nb >= 4 ? 9 : 8; }
 
-const void* kernel16(int dtype, int side, int nb, int j1, int fast, int mt, bool batch) {
+const void* kernel16(int dtype, int side, int nb, int j1, int ld, int mt, bool batch) {
   if (dtype == NNCP_BF16)
-    return mt ? pm16_kernel_form<NNCP_BF16, true>(side, nb, j1, fast, batch)
-              : pm16_kernel_form<NNCP_BF16, false>(side, nb, j1, fast, batch);
-  return mt ? pm16_kernel_form<NNCP_F16, true>(side, nb, j1, fast, batch)
-            : pm16_kernel_form<NNCP_F16, false>(side, nb, j1, fast, batch);
+    return mt ? pm16_kernel_form<NNCP_BF16, true>(side, nb, j1, ld, batch)
+              : pm16_kernel_form<NNCP_BF16, false>(side, nb, j1, ld, batch);
+  return mt ? pm16_kernel_form<NNCP_F16, true>(side, nb, j1, ld, batch)
+            : pm16_kernel_form<NNCP_F16, false>(side, nb, j1, ld, batch);
 }
 
 void allow_big_lds(const void* k) { pm_allow_lds(k, 160 * 1024); }
@@ -39,10 +39,29 @@ bool pm16_fast(int side, int64_t IL, int I1, int nb) {
   if (I1 % pm_16_kstep(side) != 0) return false;
   return side == 1 || IL % left_tr16(nb) == 0;
 }
+// Lane offsets of the range-checked form (up to 31 columns of I_L elements and a
+// row on the left, the wave's columns of I_L elements on the right) fit 31 bits.
+bool pm16_buf(int side, int64_t IL, int nb, int j1) {
+  const int64_t cols = side == 0 ? 31 : pm_16_wave_rows(1, nb, j1);
+  return (cols * IL + 256) * 2 < ((int64_t)1 << 31);
+}
 size_t pm_16_reduce_lds(int side, int nb, int wm) {
   if (wm >= 4) return 0;  // (also every J == 1 launch: one wave per column range)
   const int nacc = side == 0 ? left_tr16(nb) * nb : right_mc16(nb) * nb;
   return (size_t)wm * nacc * 4 * 64 * sizeof(double);
+}
+
+// Which loads a launch uses (pm16_body.hpp: 0 masked, 1 plain, 2 range-checked):
+// plain ones for a right node, or a left node whose columns start on cache lines,
+// if the shape allows them; range-checked without the streaming hint for the rest.
+// F16 83x71x57x45 R = 24 left node 34.9 -> 28.7 us, BF16 200x180x220 R = 32 right
+// node 39.9 -> 27.0, BF16 30012x1200x48 R = 10 right node 1361 -> 843 us against
+// the masked loads with the hint (1338 range-checked with it).
+static int load_form(const PmLaunch& L, int64_t IL, int I1) {
+  const bool fast = pm16_fast(L.side, IL, I1, L.nb);
+  if (fast && (L.side == 1 || IL % 64 == 0)) return 1;
+  if (pm16_buf(L.side, IL, L.nb, L.j1)) return 2;
+  return fast ? 1 : 0;
 }
 
 hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
@@ -51,12 +70,12 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const bool bf = L.dtype == NNCP_BF16;
   PackArgs pa{a.krp.f[0], a.I1, a.I1pad, a.R, a.col0, RP, a.hpack, a.hscale};
   const int wm = a.wm;
-  const bool fast = pm16_fast(L.side, a.IL, a.I1, L.nb);
+  const int ld = load_form(L, a.IL, a.I1);
   const bool mt = L.mper > 1;
-  // variant = j1*100000 + bf16*10000 + side*1000 + nb*100 + mt*10 + fast
+  // variant = j1*100000 + bf16*10000 + side*1000 + nb*100 + mt*10 + load form
   const int variant =
-      (L.j1 ? 100000 : 0) + (bf ? 10000 : 0) + L.side * 1000 + L.nb * 100 + (mt ? 10 : 0) + (fast ? 1 : 0);
-  const void* k = kernel16(L.dtype, L.side, L.nb, L.j1, fast, mt, false);
+      (L.j1 ? 100000 : 0) + (bf ? 10000 : 0) + L.side * 1000 + L.nb * 100 + (mt ? 10 : 0) + ld;
+  const void* k = kernel16(L.dtype, L.side, L.nb, L.j1, ld, mt, false);
   if (!k || (wm != 1 && wm != 4) || (L.j1 && wm != 4)) return hipErrorInvalidValue;
   size_t lds = L.lds_bytes;
   if (pm_16_reduce_lds(L.side, L.nb, wm) > lds) lds = pm_16_reduce_lds(L.side, L.nb, wm);
@@ -89,8 +108,10 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   }
   {
     void* pargs[] = {(void*)&pa};
-    hipError_t e = hipLaunchKernel(bf ? pm16_pack_kernel<NNCP_BF16>(false) : pm16_pack_kernel<NNCP_F16>(false),
-                                   dim3(RP), dim3(256), pargs, 0, sk.st);
+    // one group per column: 1024 threads for a long one (I_1 = 30012: 52 us with 256)
+    const int pt = a.I1pad > 2048 ? 1024 : 256;
+    hipError_t e = hipLaunchKernel(bf ? pm16_pack_kernel<NNCP_BF16>(false, pt) : pm16_pack_kernel<NNCP_F16>(false, pt),
+                                   dim3(RP), dim3(pt), pargs, 0, sk.st);
     if (e != hipSuccess) return e;
   }
   allow_big_lds(k);
@@ -108,7 +129,7 @@ const void* pm16_batch_kernel(int variant) {
 }
 
 const void* pm16_pack_batch_kernel(int variant) {
-  return variant ? pm16_pack_kernel<NNCP_BF16>(true) : pm16_pack_kernel<NNCP_F16>(true);
+  return variant ? pm16_pack_kernel<NNCP_BF16>(true, 256) : pm16_pack_kernel<NNCP_F16>(true, 256);
 }
 
 }  // namespace nncpk

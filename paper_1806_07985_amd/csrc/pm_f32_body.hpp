@@ -33,16 +33,22 @@
 namespace nncpk {
 namespace pm32 {
 
-// How the tensor is loaded. LD_BUF: range-checked buffer loads, which read zeros
-// past the tensor's end, for shapes whose lane offsets fit 31 bits (pm_f32_buf):
-// a lane's offsets are fixed per tile, so a step costs scalar address arithmetic
-// only, and no branch stands between the loads and their use.
-// LD_FAST: plain vector loads, where the shape guarantees that all of them lie
-// inside the tensor (pm_f32_fast). LD_GEN: a uniform check per step and masked
-// loads in the steps that reach the tensor's end; its branches make the compiler
-// wait for all loads in flight once per ring round; it serves columns of hundreds
-// of MB.
-enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2 };
+// How the tensor is loaded. LD_BUF, LD_BUFNT: range-checked buffer loads, which
+// read zeros past the tensor's end, for shapes whose lane offsets fit 31 bits
+// (pm_f32_buf): a lane's offsets are fixed per tile, so a step costs scalar address
+// arithmetic only, and no branch stands between the loads and their use. LD_FAST:
+// plain vector loads, where the shape guarantees that all of them lie inside the
+// tensor (pm_f32_fast). LD_GEN: a uniform check per step and masked loads in the
+// steps that reach the tensor's end; its branches make the compiler wait for all
+// loads in flight once per ring round; it serves columns of hundreds of MB.
+// The streaming (nontemporal) hint goes with LD_FAST and LD_BUFNT on the left,
+// where a tensor's columns start on cache lines: every line is then read once, by
+// one load (128^4 left node 0.18 ms with the hint, 0.20 without; 1024^3 0.69 and
+// 0.79). Everywhere else a line is read by two loads, of neighbouring rows or
+// steps, or by a step's two halves on the right, and the hint drops it in between:
+// right node of 1000x999x300 R = 20 401 -> 276 us without it, of 1024^3 R = 32
+// 1036 -> 955, of 137x201x90 R = 16 24.1 -> 19.7.
+enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2, LD_BUFNT = 3 };
 template <int L, bool NTL>
 __device__ __forceinline__ f32v<L> buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   constexpr int aux = NTL ? kBufNt : 0;
@@ -142,7 +148,7 @@ __device__ __forceinline__ void pm_left_f32_body(const PmArgs& a, int bx, int by
   auto load = [&](vT (&A)[4]) {
     const int64_t colbase = (int64_t)a.I1 * (j0 + jl) + i1_0 + KS * tl;
     const float* base = X + Mtot * colbase;
-    if constexpr (LD == LD_BUF) {
+    if constexpr (LD == LD_BUF || LD == LD_BUFNT) {
       const int64_t e0 = Mtot * colbase + (int64_t)(tile0 + tileL) * mtile + wm * WROWS;
       const __amdgpu_buffer_rsrc_t rs = buf_rsrc<4>(X + e0, IX - e0);
 #pragma unroll
@@ -177,7 +183,7 @@ __device__ __forceinline__ void pm_left_f32_body(const PmArgs& a, int bx, int by
         if (++tileL == ntile) tileL = 0;
         m = (int64_t)(tile0 + tileL) * mtile + wm * WROWS + TR * li;
         mload = m < Mtot ? m : 0;
-        if constexpr (LD == LD_BUF) set_voff();
+        if constexpr (LD == LD_BUF || LD == LD_BUFNT) set_voff();
       }
     }
   };
@@ -376,7 +382,7 @@ __device__ __forceinline__ void pm_right_f32_body(const PmArgs& a, int bx, int b
   auto load = [&](vT (&A)[MC][2]) {
     const int i1s = (ib0 + stL) * a.i1blk;
     const int64_t lbase = (int64_t)a.I1 * (j0 + jl) + i1s + KS * tl;
-    if constexpr (LD == LD_BUF) {
+    if constexpr (LD == LD_BUF || LD == LD_BUFNT) {
       const __amdgpu_buffer_rsrc_t rs = buf_rsrc<4>(X + cwk + lbase, IX - cwk - lbase);
 #pragma unroll
       for (int h = 0; h < 2; ++h)
@@ -535,24 +541,21 @@ __device__ __forceinline__ void pm_right_f32_body(const PmArgs& a, int bx, int b
 
 // Stand-alone kernels: one work-group per (M tile group, split). MT: a group
 // streams several M tiles (a separate form, so that the one-tile kernels keep
-// their register budget). NTL: tensor loads with the nontemporal (streaming)
-// hint. The stand-alone kernels stream one large tensor and use it; the batched
-// kernels do not: their items are a few hundred KB of many small tensors, several
-// launches stream at once, and with the hint the caches dropped lines (or line
-// halves) that the next k-step still needed (256-job batch: 11.2 -> 9.0 GB
-// fetched per tick, 3.24 -> 2.56 ms; the 128^4 left node alone is 0.18 ms with
-// the hint, 0.20 without). A batched right node keeps two k-steps in flight
+// their register budget). NTL: tensor loads with the streaming hint (above). The
+// batched kernels load without it: several launches stream many small tensors at
+// once, and with it 11.2 instead of 9.0 GB were fetched per tick of the 256-job
+// batch (3.24 -> 2.56 ms). A batched right node keeps two k-steps in flight
 // instead of three: its lanes' 128-byte runs start anywhere in a cache line, so a
 // line is needed by two steps, and with three the lines in flight of a die's 32
 // CUs (8 MB) pass its L2 (256-job tick 2.52 -> 2.48 ms).
-template <int SIDE, int NB, int LD, bool MT, bool NTL>
+template <int SIDE, int NB, int LD, bool MT, bool NTL, bool BATCH>
 __device__ __forceinline__ void pm_f32_body(const PmArgs& a, int bx, int by) {
   if constexpr (SIDE == 0) pm_left_f32_body<NB, left_pf(NB), LD, MT, NTL>(a, bx, by);
-  else pm_right_f32_body<NB, NTL ? right_pf(NB) : 2, LD, MT, NTL>(a, bx, by);  // (batched: two steps in flight)
+  else pm_right_f32_body<NB, BATCH ? 2 : right_pf(NB), LD, MT, NTL>(a, bx, by);
 }
 template <int SIDE, int NB, int LD, bool MT>
 __global__ __launch_bounds__(NT, 2) void pm_f32(PmArgs a) {
-  pm_f32_body<SIDE, NB, LD, MT, true>(a, blockIdx.x, blockIdx.y);
+  pm_f32_body<SIDE, NB, LD, MT, SIDE == 0 && (LD == LD_FAST || LD == LD_BUFNT), false>(a, blockIdx.x, blockIdx.y);
 }
 
 // Persistent batched form of the same kernel: work-group b takes the items
@@ -561,7 +564,7 @@ __global__ __launch_bounds__(NT, 2) void pm_f32(PmArgs a) {
 template <int SIDE, int NB, int LD, bool MT>
 __global__ __launch_bounds__(NT, 2) void pm_f32_items(const BItem* __restrict__ items, const int* __restrict__ grp,
                                                       const KOp* __restrict__ ops) {
-  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { pm_f32_body<SIDE, NB, LD, MT, false>(a, bx, by); });
+  pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { pm_f32_body<SIDE, NB, LD, MT, false, true>(a, bx, by); });
 }
 
 template <int SIDE, int LD, bool MT>
@@ -570,6 +573,16 @@ const void* pick(int nb, bool batch) {
     case 1: return batch ? (const void*)pm_f32_items<SIDE, 1, LD, MT> : (const void*)pm_f32<SIDE, 1, LD, MT>;
     case 2: return batch ? (const void*)pm_f32_items<SIDE, 2, LD, MT> : (const void*)pm_f32<SIDE, 2, LD, MT>;
     case 4: return batch ? (const void*)pm_f32_items<SIDE, 4, LD, MT> : (const void*)pm_f32<SIDE, 4, LD, MT>;
+    default: return nullptr;
+  }
+}
+
+template <bool MT>
+const void* pick_nt(int nb) {
+  switch (nb) {
+    case 1: return (const void*)pm_f32<0, 1, LD_BUFNT, MT>;
+    case 2: return (const void*)pm_f32<0, 2, LD_BUFNT, MT>;
+    case 4: return (const void*)pm_f32<0, 4, LD_BUFNT, MT>;
     default: return nullptr;
   }
 }
@@ -583,6 +596,9 @@ const void* pm_f32_form(int nb, int ld, bool batch) {
   switch (ld) {
     case pm32::LD_FAST: return pm32::pick<SIDE, pm32::LD_FAST, MT>(nb, batch);
     case pm32::LD_BUF: return pm32::pick<SIDE, pm32::LD_BUF, MT>(nb, batch);
+    case pm32::LD_BUFNT:  // stand-alone left nodes
+      if (SIDE == 0 && !batch) return pm32::pick_nt<MT>(nb);
+      return pm32::pick<SIDE, pm32::LD_BUF, MT>(nb, batch);
     default: return pm32::pick<SIDE, pm32::LD_GEN, MT>(nb, batch);
   }
 }

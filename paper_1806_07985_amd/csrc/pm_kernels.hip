@@ -384,16 +384,17 @@ bool pm_f32_buf(int side, int64_t IL, int nb) {
   const int64_t cols = side == 0 ? 15 : 16 * right_mc(nb);  // lane offsets reach this many columns of I_L elements
   return (cols * IL + 64 * 4) * 4 < ((int64_t)1 << 31);
 }
-// Which loads a launch uses. Range-checked where the offsets fit: against the
-// masked ones, left node of 1000x999x300 R = 20 0.288 -> 0.251 ms, of 137x201x90
-// R = 16 29.8 -> 24.6 us; against the plain ones, left node of 1024^3 (one wave
-// along M) 0.79 -> 0.69 ms, 512^3 R = 10 equal. A left node with four waves along
-// M keeps the plain loads where the shape allows them: 128^4 takes 0.437 ms per
-// iteration with them and 0.443 range-checked, 64^5 1.72 and 1.73.
+// Which loads a launch uses (pm_f32_body.hpp). Range-checked where the offsets fit,
+// with the streaming hint on the left if columns start on cache lines: against the
+// masked ones, left node of 1000x999x300 R = 20 0.288 -> 0.245 ms, of 137x201x90
+// R = 16 29.8 -> 23.3 us; against the plain ones, left node of 1024^3 0.79 -> 0.69
+// ms, 512^3 R = 10 equal. Left nodes with columns of 16 KB and more keep the plain
+// loads where the shape allows them: 64^5 (16 KB) takes 1.72 ms per iteration with
+// them and 1.78 range-checked, 128^4 (64 KB) 0.438 and 0.457.
 static int load_form(const PmLaunch& L, int64_t IL, int I1) {
-  const bool fast = pm_f32_fast(L.side, IL, I1, L.nb, L.xs);
-  if (fast && L.side == 0 && L.wm == 4) return LD_FAST;
-  if (pm_f32_buf(L.side, IL, L.nb)) return LD_BUF;
+  const bool fast = pm_f32_fast(L.side, IL, I1, L.nb, L.xs), lines = L.side == 0 && IL % 32 == 0;
+  if (fast && lines && IL >= 4096) return LD_FAST;
+  if (pm_f32_buf(L.side, IL, L.nb)) return lines ? LD_BUFNT : LD_BUF;
   return fast ? LD_FAST : LD_GEN;
 }
 

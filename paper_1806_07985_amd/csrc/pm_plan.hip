@@ -145,6 +145,11 @@ static PmLaunch plan_impl(int side, int dtype, int64_t IL, int64_t IR, int I1, i
     } else if (L.j1 && L.istages == 1 && L.mtiles >= target && L.nb < 4) {
       // (the J == 1 kernel at four column blocks has no registers to spare for it)
       L.mper = (int)cdiv(L.mtiles, target);
+    } else if (L.j1 && L.istages == 1 && L.nb < 4 && (int64_t)L.mtiles * n_i1grp > target) {
+      // K split over i1 blocks of up to 150 KB of LDS each: one round of groups,
+      // each staging its block once for several tiles, instead of a group per
+      // tile (57600 x 30012 R = 10: 2147 groups, 8.4 rounds)
+      L.mper = (int)cdiv((int64_t)L.mtiles * n_i1grp, target);
     }
   }
   L.wm = wm;

@@ -1,5 +1,5 @@
-"""Range-checked tensor loads of the FP32 partial-MTTKRP kernels: a host walk of
-every lane offset, and on the GPU ragged tensors that lie between NaNs."""
+"""Range-checked tensor loads of the partial-MTTKRP kernels: a host walk of every
+lane offset (FP32), and on the GPU ragged tensors that lie between NaNs."""
 
 import os
 import subprocess
@@ -47,3 +47,30 @@ def test_ragged_tensor_between_nans(gpu_lib, dims, R, s, side):
     ref = fn(X.astype(np.float64), [h.astype(np.float64) for h in H], s).reshape(-1, R, order="F")
     # positive data: FP32 chains of up to 2^7 products, each rounding at most 2^-24 of the sum
     assert np.all(np.abs(T - ref) <= 2.0 ** -17 * ref), float(np.max(np.abs(T - ref) / ref))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,R,s", SHAPES + [((301, 70), 10, 1), ((129, 9001), 10, 1)])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_ragged_16bit_tensor_between_nans(gpu_lib, dims, R, s, dt):
+    """The range check drops a dword that is half inside: a tensor of odd extents
+    ends in one, and its last element has to count all the same."""
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case buffer loads {dt} dims={dims} R={R} s={s}", flush=True)
+    rng = np.random.default_rng(sum(dims) + R + s)
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32)).to(tdt)
+    X[-1] = 100.0  # large: leaving the last element out would show
+    X64 = X.double().numpy().reshape(dims, order="F")
+    H = [rng.random((d, R)).astype(np.float32) for d in dims]
+    Hd = [native.factor_to_device(h) for h in H]
+    for at in (10002, 10003):  # even and odd element offsets
+        room = torch.full((X.numel() + 20011,), float("nan"), device="cuda", dtype=tdt)
+        Xd = room[at:at + X.numel()]
+        Xd.copy_(X)
+        for side, fn in ((0, O.partial_mttkrp_left), (1, O.partial_mttkrp_right)):
+            T = native.partial_mttkrp(Xd, list(dims), s, side, Hd, R).cpu().numpy().T
+            ref = fn(X64, [h.astype(np.float64) for h in H], s).reshape(-1, R, order="F")
+            # the 16-bit path's bound: 2e-6 of sum |x||k| (all positive here)
+            assert np.all(np.abs(T - ref) <= 2e-6 * ref), (side, at, float(np.max(np.abs(T - ref) / ref)))
