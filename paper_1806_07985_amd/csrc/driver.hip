@@ -230,7 +230,17 @@ Layout make_layout(const Problem& p) {
   L.off_S = take(sizeof(double) * N * RR);
   L.off_fit = take(sizeof(double) * kFitCap);
   L.off_finpart = take(sizeof(double) * (size_t)maxchunks * (RR + 1));
-  L.off_pmpart = take(sizeof(double) * std::max(L.pmL[0].partial_doubles, L.pmL[1].partial_doubles));
+  // split sums: of the partial MTTKRPs, and of trailing multi-TTVs over a long J
+  // (used one after the other)
+  build_tree(p, L);
+  size_t part0 = std::max(L.pmL[0].partial_doubles, L.pmL[1].partial_doubles);
+  for (int i = 0; i < L.ntn; ++i)
+    if (L.tn[i].kind == T_TRAIL) {
+      const int64_t J = prod_range(p, L.tn[i].b + 1, L.tn[L.tn[i].parent].b);
+      const int nz = mttv_trail_split(L.tn[i].rows, J, R);
+      if (nz > 1) part0 = std::max(part0, (size_t)nz * (size_t)L.tn[i].rows * R);
+    }
+  L.off_pmpart = take(sizeof(double) * part0);
   L.off_hpack = take(std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes));
   // the scale table of a partial MTTKRP (the largest root launch)
   size_t tab = std::max(pm_sctab_doubles(L.pmL[0]), pm_sctab_doubles(L.pmL[1]));
@@ -240,7 +250,6 @@ Layout make_layout(const Problem& p) {
   for (int k = 0; k < N; ++k) maxI = std::max(maxI, p.dims[k]);
   L.off_M = take(sizeof(double) * (size_t)maxI * R);
   L.node_f64 = p.dtype == NNCP_F32 ? 1 : 0;
-  build_tree(p, L);
   for (int i = 0; i < L.ntn; ++i)
     if (L.tn[i].has_buf) L.tn[i].off = take((size_t)L.tn[i].rows * R * (L.node_f64 ? 8 : 4));
   L.off_dtA = L.off_dtB = 0;
@@ -270,11 +279,15 @@ Layout make_layout(const Problem& p) {
     const size_t tb = (size_t)tmax * R * (L.node_f64 ? 8 : 4);
     L.off_dtA = take(tb);
     L.off_dtB = take(tb);
-    if (part > std::max(L.pmL[0].partial_doubles, L.pmL[1].partial_doubles) ||
+    for (int n = 0; n < N - 1; ++n)
+      if (L.dside[n] == 1) {
+        const int nz = mttv_trail_split(p.dims[n], prod_range(p, n + 1, N - 1), R);
+        if (nz > 1) part = std::max(part, (size_t)nz * (size_t)p.dims[n] * R);
+      }
+    if (part > part0 ||
         pack > std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes)) {
       // relocate the partial and pack regions to fit the no-tree launches too
-      L.off_pmpart = take(sizeof(double) * std::max(part, std::max(L.pmL[0].partial_doubles,
-                                                                    L.pmL[1].partial_doubles)));
+      L.off_pmpart = take(sizeof(double) * std::max(part, part0));
       L.off_hpack = take(std::max(pack, std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes)));
     }
   }
@@ -421,6 +434,7 @@ hipError_t direct_mttkrp(const nncp_plan* P, int n, bool scaled, const Sink& st0
   a.J = prod_range(p, n + 1, p.N - 1);
   a.R = p.R;
   a.krp = krp_for(P, n + 1, p.N - 1, scaled);
+  a.part = P->pmpart();
   a.out = P->Mbuf();
   a.out_f64 = 1;
   *M = P->Mbuf();
@@ -453,6 +467,7 @@ hipError_t tree_op(const nncp_plan* P, int i, bool scaled, const Sink& st, const
     a.Ia = t.rows;
     a.J = prod_range(p, t.b + 1, q.b);
     a.krp = krp_for(P, t.b + 1, q.b, scaled);
+    a.part = P->pmpart();
   } else {  // contract modes q.a..a-1 of the parent, keep a..b
     a.Ia = prod_range(p, q.a, t.a - 1);
     a.J = t.rows;

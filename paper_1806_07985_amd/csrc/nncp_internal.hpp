@@ -161,7 +161,14 @@ struct MttvArgs {
   KrpDesc krp;          // trail: the contracted last modes; lead: the contracted first modes (first fastest)
   void* out;
   int out_f64;          // out is double (else float)
+  // trailing multi-TTVs: scratch for nz x R x Ia FP64 partials, or nullptr for an
+  // unsplit J; nz runs of jz (set by the launch)
+  double* part;
+  int nz;
+  int64_t jz;
 };
+// Runs of J a trailing multi-TTV is split into (1: unsplit).
+int mttv_trail_split(int64_t Ia, int64_t J, int R);
 hipError_t mttv_trail_launch(const MttvArgs& a, hipStream_t st);
 hipError_t mttv_lead_launch(const MttvArgs& a, hipStream_t st);
 hipError_t mttv_trail_launch(const MttvArgs& a, const Sink& sk);
@@ -267,7 +274,7 @@ enum KKind : int {
   K_PM_REDUCE = 4,  // variant: t_f64
   K_MTTV_TRAIL = 5, // variant: t_f64
   K_MTTV_LEAD = 6,  // variant: group size * 10 + t_f64
-  K_UPDATE = 7,     // variant: R > 64: values per lane (1, 2); R <= 64: register columns (16, 32, 64)
+  K_UPDATE = 7,     // variant: R > 64: values per lane (1, 2); R <= 64: register columns (16, 32, 64), + 100: a lane per row
   K_FIN_FUSED = 9,  // R > 64: one row chunk
   K_GRAM_CHUNKS = 10,
   K_FIN_TAIL = 11,

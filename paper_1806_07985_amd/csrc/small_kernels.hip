@@ -159,17 +159,23 @@ __global__ void unit_lambda_kernel(double* lam, int64_t n) {
 // --------------------------------------------------------------------------
 constexpr int TRAIL_KCH = 1024;
 
+// A node with few rows and a long J is split over nz runs of J (FP64 partials,
+// added in order by the split-K sum kernel): one group per 64 rows and column
+// leaves the chip idle then (64 rows, J = 262144 / 64, R = 32: 32 groups, 105 us).
 template <typename TN>
-__device__ __forceinline__ void mttv_trail_body(const MttvArgs& a, int bx, int r) {
+__device__ __forceinline__ void mttv_trail_body(const MttvArgs& a, int bxz, int r) {
   __shared__ double kv[TRAIL_KCH];
   __shared__ double red[4][64];
   const int ti = threadIdx.x & 63, ph = threadIdx.x >> 6;
+  const int bx = a.nz > 1 ? bxz / a.nz : bxz, z = a.nz > 1 ? bxz - bx * a.nz : 0;
+  const int64_t jb = a.nz > 1 ? (int64_t)z * a.jz : 0;
+  const int64_t je = a.nz > 1 && jb + a.jz < a.J ? jb + a.jz : a.J;
   const int64_t i = (int64_t)bx * 64 + ti;
   const double scale = krp_colscale(a.krp, r);
   const TN* Tr = as_global((const TN*)a.T) + (int64_t)r * a.Ia * a.J;
   double acc = 0.0;
-  for (int64_t j0 = 0; j0 < a.J; j0 += TRAIL_KCH) {
-    const int cnt = (int)((a.J - j0) < TRAIL_KCH ? (a.J - j0) : TRAIL_KCH);
+  for (int64_t j0 = jb; j0 < je; j0 += TRAIL_KCH) {
+    const int cnt = (int)((je - j0) < TRAIL_KCH ? (je - j0) : TRAIL_KCH);
     __syncthreads();
     // the Khatri-Rao column chunk: every factor load is issued (from a valid
     // address) before any product is formed
@@ -215,7 +221,8 @@ __device__ __forceinline__ void mttv_trail_body(const MttvArgs& a, int bx, int r
   __syncthreads();
   if (ph == 0 && i < a.Ia) {
     double s = red[0][ti] + red[1][ti] + red[2][ti] + red[3][ti];
-    stv(a.out, i + a.Ia * r, a.out_f64, s);
+    if (a.nz > 1) as_global(a.part)[((int64_t)z * a.R + r) * a.Ia + i] = s;
+    else stv(a.out, i + a.Ia * r, a.out_f64, s);
   }
 }
 template <typename TN>
@@ -435,6 +442,11 @@ __global__ __launch_bounds__(NT) void update_kernel(UpdateArgs a) {
 // or k >= R), invd = 1 / S(k, k) (zero unless positive). The column sweeps are
 // unrolled over RB, so every broadcast uses a constant lane and the Gauss-Seidel
 // chain touches no memory. Returns the new w.
+// The row's latency is the chain of R column steps, so the chain is kept short:
+// lanes hold the residual y = m - (w S) instead of m and w S, and column r's change
+// is max(y / S(r,r), -w), which is W(:,r) <- max(0, W(:,r) + (M(:,r) - (W S)(:,r)) /
+// S(r,r)) written as a difference: two operations, a broadcast and one update of y
+// per step (1344 rows, R = 50: 11.6 -> 10.5 us).
 // With tol > 0 the sweeps stop early, once a sweep changes no entry of the row
 // by more than tol times the row's largest entry (the row is one NNLS
 // subproblem of the block; the rows are independent).
@@ -446,12 +458,22 @@ template <int RB>
 __device__ __forceinline__ double update_row_reg(double w, const double m, const double (&srow)[RB],
                                                  const double invd, const int k, const int R, const int update,
                                                  const int sweeps, const double tol) {
-  double g = 0.0;
+  auto wS = [&]() {  // w S, two sums
+    double g0 = 0.0, g1 = 0.0;
 #pragma unroll
-  for (int r = 0; r < RB; ++r) g += readlane_f64(w, r) * srow[r];
+    for (int r = 0; r < RB; r += 2) {
+      g0 += readlane_f64(w, r) * srow[r];
+      g1 += readlane_f64(w, r + 1) * srow[r + 1];
+    }
+    return g0 + g1;
+  };
   if (update == NNCP_HALS) {
+    double y = m - wS();
+    // a zero diagonal (all-zero column elsewhere) sets the column to zero: its
+    // candidate change is -inf, so the maximum is -w
+    const double bias = invd > 0.0 ? 0.0 : -__builtin_huge_val();
     double dmax = 0.0;  // a sweep's largest |change| (uniform: every change is broadcast)
-    auto sweep = [&]() {
+    auto sweep = [&](bool track) {
       // fresh copies of the lane index and the rank per sweep: the per-column
       // compares below then stay inside the sweep instead of being hoisted out of
       // the sweep loop into 64 live lane masks
@@ -461,34 +483,26 @@ __device__ __forceinline__ double update_row_reg(double w, const double m, const
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         if (r < Rv) {  // uniform
-          // column r: W(:,r) <- max(0, W(:,r) + (M(:,r) - (W S)(:,r)) / S(r,r)); a zero
-          // diagonal sets the column to zero (lane r owns column r)
-          double wn = invd > 0.0 ? w + (m - g) * invd : 0.0;
-          wn = wn > 0.0 ? wn : 0.0;
-          const double dlt = readlane_f64(wn - w, r);
-          dmax = fmax(dmax, fabs(dlt));
+          const double dlt = readlane_f64(fmax(__builtin_fma(y, invd, bias), -w), r);
+          y = __builtin_fma(-dlt, srow[r], y);
           if (kv == r) w += dlt;
-          g += dlt * srow[r];
+          if (track) dmax = fmax(dmax, fabs(dlt));
         }
       }
     };
-    // g stays equal to w S across sweeps: every column change is added to it
+    // y stays m - w S across sweeps: every column change is taken off it
     if (tol > 0.0) {
       for (int sw = 0; sw < sweeps; ++sw) {
         dmax = 0.0;
-        sweep();
+        sweep(true);
         if (dmax <= tol * wave_max_f64(fabs(w))) break;  // uniform
       }
     } else {
-      for (int sw = 0; sw < sweeps; ++sw) sweep();
+      for (int sw = 0; sw < sweeps; ++sw) sweep(false);
     }
   } else {
     for (int sw = 0; sw < sweeps; ++sw) {
-      if (sw > 0) {
-        g = 0.0;
-#pragma unroll
-        for (int r = 0; r < RB; ++r) g += readlane_f64(w, r) * srow[r];
-      }
+      const double g = wS();
       const double den = g > 1e-16 ? g : 1e-16;
       const double wn = w * m / den;
       const double d = fabs(wn - w);
@@ -536,10 +550,120 @@ __device__ __forceinline__ void update_reg_body(const UpdateArgs& a, int bx) {
     if (a.W64) a.W64[row + a.I * k] = w;
   }
 }
+// The update for R <= RB <= 32 and many rows: one lane per row. The lane holds the
+// whole row of W in registers and forms (W S)(:,r) afresh for every column from S
+// in LDS (read by broadcast, two entries per load), so a wave updates 64 rows with
+// R multiply-adds per column instead of one row with a broadcast chain per column,
+// and its loads of M and W are 64 consecutive rows of a column. 30012 rows, R = 10:
+// one wave per row 23.7 us (each wave reads a line per column for one row), so 6.
+template <int RB>
+__device__ __forceinline__ void update_lane_body(const UpdateArgs& a, int bx) {
+  __shared__ double Sl[RB * RB], inv[RB], low[RB], fs[RB];  // low: 0, or -inf where a column is set to zero
+  const int R = a.R;
+  const int64_t row = (int64_t)bx * NT + threadIdx.x;
+  const bool live = row < a.I;
+  const int64_t rc = live ? row : a.I - 1;
+  double w[RB], m[RB];
+#pragma unroll
+  for (int k = 0; k < RB; ++k) {
+    const int kc = k < R ? k : 0;
+    w[k] = (double)a.W[rc + a.I * kc];
+  }
+  // (one branch for all of M's loads: a branch around each would wait for each)
+  if (a.m_f64) {
+    const double* Mp = as_global((const double*)a.M) + rc;
+#pragma unroll
+    for (int k = 0; k < RB; ++k) m[k] = Mp[a.I * (k < R ? k : 0)];
+  } else {
+    const float* Mp = as_global((const float*)a.M) + rc;
+    float mf[RB];
+#pragma unroll
+    for (int k = 0; k < RB; ++k) mf[k] = Mp[a.I * (k < R ? k : 0)];
+#pragma unroll
+    for (int k = 0; k < RB; ++k) m[k] = (double)mf[k];
+  }
+  for (int e = threadIdx.x; e < RB * RB; e += NT) {
+    const int r = e / RB, k = e % RB;
+    Sl[e] = r < R && k < R ? a.S[r * R + k] : 0.0;
+  }
+  if (threadIdx.x < RB) {
+    const int k = threadIdx.x < R ? threadIdx.x : 0;
+    const double d = a.S[k * R + k];
+    inv[threadIdx.x] = d > 0.0 ? 1.0 / d : 0.0;
+    low[threadIdx.x] = d > 0.0 ? 0.0 : -__builtin_huge_val();
+    const double ls = a.lam_self[k], lm = a.lam_model[k];
+    fs[threadIdx.x] = threadIdx.x < R && ls > 0.0 ? lm / ls : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < RB; ++k) w[k] *= fs[k];
+  // `z` is zero, but not to the compiler: S stays in LDS instead of being hoisted
+  // out of the sweeps into registers that there are not
+  int z = 0;
+  auto dot = [&](int r) {  // (w S)(r), four sums
+    double g[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < RB; ++k) g[k & 3] = __builtin_fma(w[k], Sl[z + r * RB + k], g[k & 3]);
+    __builtin_amdgcn_sched_barrier(0);
+    return (g[0] + g[1]) + (g[2] + g[3]);
+  };
+  const int sweeps = a.sweeps > 1 ? a.sweeps : 1;
+  bool go = live;  // this row still sweeps
+  for (int sw = 0; sw < sweeps; ++sw) {
+    double dmax = 0.0, wmax = 0.0;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+    if (a.update == NNCP_HALS) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        if (r < R) {  // uniform
+          const double y = m[r] - dot(r);
+          const double d = fmax(__builtin_fma(y, inv[r], low[r]), -w[r]);
+          w[r] = go ? w[r] + d : w[r];
+          dmax = fmax(dmax, fabs(d));
+        }
+      }
+    } else {
+      double wn[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        wn[r] = 0.0;
+        if (r < R) {
+          const double g = dot(r), den = g > 1e-16 ? g : 1e-16;
+          wn[r] = w[r] * m[r] / den;
+          dmax = fmax(dmax, fabs(wn[r] - w[r]));
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < RB; ++r) w[r] = go ? wn[r] : w[r];
+    }
+    if (a.tol > 0.0) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) wmax = fmax(wmax, fabs(w[r]));
+      go = go && !(dmax <= a.tol * wmax);
+      if (!__any(go)) break;
+    }
+  }
+  if (live) {
+#pragma unroll
+    for (int k = 0; k < RB; ++k)
+      if (k < R) {
+        a.W[row + a.I * k] = (float)w[k];
+        if (a.W64) a.W64[row + a.I * k] = w[k];
+      }
+  }
+}
+template <int RB>
+__global__ __launch_bounds__(NT) void update_lane_kernel(UpdateArgs a) {
+  update_lane_body<RB>(a, blockIdx.x);
+}
+
 template <int RB>
 __global__ __launch_bounds__(NT) void update_reg_kernel(UpdateArgs a) {
   update_reg_body<RB>(a, blockIdx.x);
 }
+
+constexpr int kUpdLane = 100;         // update variants of one lane per row: 100 + registers
+constexpr int64_t kUpdLaneRows = 4096;
 
 // Rows of W staged in LDS at a time (FP64): about 32 KB.
 __host__ __device__ inline int fin_sub_rows(int R) {
@@ -656,10 +780,8 @@ __device__ void finalize_tail(const FinalizeArgs& a, double* fl, double* sh) {
   }
 }
 
-// Ranks up to this use the 1024-thread Gram kernels below (4 x 4 register blocks of W^T W).
+// Ranks up to this use the 1024-thread Gram kernels below.
 constexpr int kSmallMaxR = 64;
-
-__host__ __device__ inline int gram_r4(int R) { return (R + 3) & ~3; }
 
 // One block does both stages (a single row chunk).
 __device__ __forceinline__ void finalize_fused_body(const FinalizeArgs& a) {
@@ -684,145 +806,99 @@ __global__ __launch_bounds__(NT) void gram_chunks_kernel(FinalizeArgs a) { gram_
 __global__ __launch_bounds__(NT) void finalize_tail_kernel(FinalizeArgs a) { finalize_tail_body(a); }
 
 // ---------------------------------------------------------------------------
-// Gram, lambda, next S and the fit for R <= 64 with 1024-thread work-groups.
-// Sixteen waves per group (four per SIMD) hide one another's latencies where a
-// 4-wave group left every latency exposed; only the upper triangle of 4x4
-// blocks of W^T W is computed (the lower one is its mirror, bit for bit); and
-// every global value the group needs is requested before the first is used.
-// The staged rows have an odd stride in doubles, so a wave's column writes
-// spread over the LDS banks. Entry e of an R x R matrix belongs to thread
-// e mod 1024, slot e / 1024 (at most four slots).
+// Gram, lambda, next S and the fit for R <= 64 with 1024-thread work-groups. W^T W
+// runs on the FP64 matrix instruction (16x16x4): a wave takes one pair of 16-column
+// blocks of the upper triangle and every ns-th group of 16 rows, both operands
+// straight from global memory (a lane's four rows of one column are one 16-byte
+// load and feed four products; the order of the rows in a sum is free), and the
+// waves of a pair add up through LDS in a fixed order. These kernels are bound by
+// latency: staging the rows through LDS and 4x4 register blocks took five barriers
+// and a long chain of LDS reads (1344 x 50 in four groups: 26.5 us, one group of
+// 128 x 32: 10.4 us; now, in seven groups, 12.5 and 7.2). Entry e of an R x R matrix belongs
+// to thread e mod 1024, slot e / 1024 (at most four slots).
 constexpr int NTF = 1024;
-constexpr int kFinStage = 8192;           // staged elements (rows x R4) per round
-constexpr int kFinQS = kFinStage / NTF;   // staged elements per thread
-constexpr int kFinMaxPh = 32;             // at most this many row phases per block
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-__host__ __device__ inline int fin_nb4(int R) { return gram_r4(R) >> 2; }
-__host__ __device__ inline int fin_nblk(int R) { return fin_nb4(R) * (fin_nb4(R) + 1) / 2; }
-__host__ __device__ inline int fin_nph(int R) {
-  const int p = NTF / fin_nblk(R);
-  return p < kFinMaxPh ? p : kFinMaxPh;
-}
-__host__ __device__ inline int fin_rows(int R) { return kFinStage / gram_r4(R); }
-__host__ __device__ inline int fin_stride(int R) { return gram_r4(R) + 1; }
-// dynamic LDS doubles: the staged rows, reused for the phase partials (<= 128 KB)
-__host__ __device__ inline int fin_work_doubles(int R) {
-  const int st = fin_rows(R) * fin_stride(R), ph = 16 * fin_nph(R) * fin_nblk(R);
-  return st > ph ? st : ph;
-}
+__host__ __device__ inline int fin_nb(int R) { return (R + 15) >> 4; }
+__host__ __device__ inline int fin_pairs(int R) { return fin_nb(R) * (fin_nb(R) + 1) / 2; }
+__host__ __device__ inline int fin_ns(int R) { return 16 / fin_pairs(R); }
+// dynamic LDS doubles: one 16 x 16 block per wave (<= 32 KB)
+__host__ __device__ inline int fin_work_doubles(int R) { return fin_ns(R) * fin_pairs(R) * 256; }
 // R x R entries per thread: 1, 2 or 4
 __host__ __device__ inline int fin_ep(int R) { return R * R <= NTF ? 1 : (R * R <= 2 * NTF ? 2 : 4); }
 
-// block (bx, by), bx <= by, of upper-triangle index b (row-major over the triangle)
-__device__ __forceinline__ void tri_block(int b, int nb4, int& bx, int& by) {
-  int x = 0;
-  while (b >= nb4 - x) {
-    b -= nb4 - x;
-    ++x;
-  }
-  bx = x;
-  by = x + b;
-}
-__device__ __forceinline__ int tri_index(int bx, int by, int nb4) { return bx * nb4 - bx * (bx - 1) / 2 + (by - bx); }
+__device__ __forceinline__ int tri_index(int bx, int by, int nb) { return bx * nb - bx * (bx - 1) / 2 + (by - bx); }
 
-// Stage-load of rows [s0, s0 + cnt): element e = tid + NTF*q is (row s0 + e mod cnt,
-// column e / cnt); columns R..R4-1 are zero. Loads are unconditional (clamped index).
-__device__ __forceinline__ void fin_load(const FinalizeArgs& a, int64_t s0, int cnt, bool fit, float (&wf)[kFinQS],
-                                         double (&mv)[kFinQS]) {
-  const int R4 = gram_r4(a.R), tid = threadIdx.x;
-  const int dk = NTF / cnt, drw = NTF - dk * cnt;
-  int k = tid / cnt, rw = tid - (tid / cnt) * cnt;
+// Rows row .. row + 3 of column col in FP64, zero for rows at or past r1 and for
+// columns at or past R. `whole`: the four rows exist (a 16-byte load, aligned to
+// the element); else element loads from clamped rows.
+__device__ __forceinline__ d4 fin_rows4(const FinalizeArgs& a, int64_t row, int64_t r1, int col, bool whole) {
+  typedef float f4e __attribute__((ext_vector_type(4), aligned(4)));
+  const float* W = as_global(a.W) + a.I * (int64_t)(col < a.R ? col : 0);
+  f4e v;
+  if (whole) {
+    v = *(const f4e*)(W + row);
+  } else {
 #pragma unroll
-  for (int q = 0; q < kFinQS; ++q) {
-    const bool ok = tid + NTF * q < cnt * R4 && k < a.R;
-    const int64_t idx = ok ? s0 + rw + a.I * (int64_t)k : 0;
-    const float w = a.W[idx];
-    wf[q] = ok ? w : 0.f;
-    if (fit) {
-      const double m = ldv(a.M, idx, a.m_f64);
-      mv[q] = ok ? m : 0.0;
-    }
-    k += dk;
-    rw += drw;
-    if (rw >= cnt) {
-      rw -= cnt;
-      ++k;
-    }
+    for (int u = 0; u < 4; ++u) v[u] = W[row + u < a.I ? row + u : a.I - 1];
   }
-}
-__device__ __forceinline__ void fin_store(const FinalizeArgs& a, int cnt, const float (&wf)[kFinQS], double* work) {
-  const int R4 = gram_r4(a.R), str = R4 + 1, tid = threadIdx.x;
-  const int dk = NTF / cnt, drw = NTF - dk * cnt;
-  int k = tid / cnt, rw = tid - (tid / cnt) * cnt;
+  d4 x;
 #pragma unroll
-  for (int q = 0; q < kFinQS; ++q) {
-    if (tid + NTF * q < cnt * R4) work[rw * str + k] = (double)wf[q];
-    k += dk;
-    rw += drw;
-    if (rw >= cnt) {
-      rw -= cnt;
-      ++k;
-    }
-  }
+  for (int u = 0; u < 4; ++u) x[u] = col < a.R && row + u < r1 ? (double)v[u] : 0.0;
+  return x;
 }
 
 // W^T W over rows [r0, r1) into g[q] (entry tid + NTF*q; raw, unnormalised) and
 // beta = sum of M o W over those rows (thread 0, when the fit is due). Block-wide;
-// work: fin_work_doubles. The code is kept short on purpose: these kernels run
-// once per mode on one group, and their time follows the instruction bytes that
-// must be fetched more than the arithmetic.
+// work: fin_work_doubles.
 template <int EP>
 __device__ __forceinline__ void gram1k_rows(const FinalizeArgs& a, int64_t r0, int64_t r1, double* work, double* sh,
                                             double (&g)[EP], double& beta) {
-  const int R = a.R, RR = R * R, tid = threadIdx.x;
-  const int nb4 = fin_nb4(R), nblk = fin_nblk(R), nph = fin_nph(R), str = fin_stride(R), sub = fin_rows(R);
-  const bool active = tid < nblk * nph;
-  const int blk = tid % nblk, ph = tid / nblk;
-  int bx, by;
-  tri_block(active ? blk : 0, nb4, bx, by);
-  const bool fit = a.do_fit && a.M;
-  double acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
-  double bsum = 0.0;
-  for (int64_t s0 = r0; s0 < r1; s0 += sub) {
-    const int cnt = (int)(r1 - s0 < sub ? r1 - s0 : sub);
-    float wf[kFinQS];
-    double mv[kFinQS];
-    fin_load(a, s0, cnt, fit, wf, mv);
-    if (fit) {
-#pragma unroll
-      for (int q = 0; q < kFinQS; ++q) bsum += (double)wf[q] * mv[q];
-    }
-    __syncthreads();  // the previous round's rows are no longer read
-    fin_store(a, cnt, wf, work);
-    __syncthreads();
-    if (active) {
-      for (int r = ph; r < cnt; r += nph) {
-        const double* row = work + r * str;
-        double x[4], y[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x[i] = row[4 * bx + i];
-          y[i] = row[4 * by + i];
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] += x[i] * y[j];
+  const int R = a.R, RR = R * R, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lq = lane >> 4;
+  const int nb = fin_nb(R), np = fin_pairs(R), ns = fin_ns(R);
+  const int p = wave % np, q0 = wave / np;
+  const bool active = q0 < ns;
+  int bi = 0, bj = p;  // the pair's blocks, bi <= bj (row-major over the triangle)
+  while (bj >= nb - bi) {
+    bj -= nb - bi;
+    ++bi;
+  }
+  bj += bi;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  if (active) {
+    for (int64_t t = r0 + 16 * q0; t < r1; t += 32 * ns) {  // two row groups in flight
+      const int64_t t2 = t + 16 * ns;
+      const bool w1 = t + 16 <= a.I, w2 = t2 + 16 <= a.I;  // uniform
+      const int64_t ra = t + 4 * lq, rb = t2 + 4 * lq;
+      const d4 x0 = fin_rows4(a, ra, r1, 16 * bi + li, w1);
+      const d4 x1 = fin_rows4(a, rb, r1, 16 * bi + li, w2);
+      d4 y0 = x0, y1 = x1;
+      if (bj != bi) {
+        y0 = fin_rows4(a, ra, r1, 16 * bj + li, w1);
+        y1 = fin_rows4(a, rb, r1, 16 * bj + li, w2);
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x0[u], y0[u], acc, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x1[u], y1[u], acc, 0, 0, 0);
     }
   }
-  beta = fit ? block_sum(bsum, sh) : 0.0;
-  // phases summed in phase order through LDS: [block entry][phase][block]
-  __syncthreads();
+  beta = 0.0;
+  if (a.do_fit && a.M) {
+    const int64_t n = (r1 - r0) * R;
+    double bsum = 0.0;
+    for (int64_t e = tid; e < n; e += NTF) {
+      const int64_t k = e / (r1 - r0), idx = r0 + (e - k * (r1 - r0)) + a.I * k;
+      bsum += (double)as_global(a.W)[idx] * ldv(a.M, idx, a.m_f64);
+    }
+    beta = block_sum(bsum, sh);
+  }
+  // acc[v]: row 4v + lq, column li of the block; splits summed in order
   if (active) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) work[((i * 4 + j) * nph + ph) * nblk + blk] = acc[i][j];
+    for (int v = 0; v < 4; ++v) work[(q0 * np + p) * 256 + (4 * v + lq) * 16 + li] = acc[v];
   }
   __syncthreads();
 #pragma unroll
@@ -830,18 +906,11 @@ __device__ __forceinline__ void gram1k_rows(const FinalizeArgs& a, int64_t r0, i
     const int e = tid + NTF * q;
     const int ec = e < RR ? e : 0;
     const int x = ec / R, y = ec - (ec / R) * R;
-    const int X = x >> 2, Y = y >> 2;
-    const int b = X <= Y ? tri_index(X, Y, nb4) : tri_index(Y, X, nb4);
-    const int qv = X <= Y ? (x & 3) * 4 + (y & 3) : (y & 3) * 4 + (x & 3);
-    const double* src = work + (size_t)qv * nph * nblk + b;
+    const int X = x >> 4, Y = y >> 4;
+    const int b = X <= Y ? tri_index(X, Y, nb) : tri_index(Y, X, nb);
+    const int at = X <= Y ? (x & 15) * 16 + (y & 15) : (y & 15) * 16 + (x & 15);
     double s = 0.0;
-    for (int p0 = 0; p0 < nph; p0 += 8) {  // eight loads in flight, added in order
-      double t[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(p0 + u < nph ? p0 + u : 0) * nblk];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += p0 + u < nph ? t[u] : 0.0;
-    }
+    for (int c = 0; c < ns; ++c) s += work[(c * np + b) * 256 + at];
     g[q] = s;
   }
 }
@@ -860,6 +929,11 @@ __device__ __forceinline__ void fin_preload(const FinalizeArgs& a, FinPre<EP>& p
   const int RR = a.R * a.R, tid = threadIdx.x;
 #pragma unroll
   for (int q = 0; q < EP; ++q) p.P[q] = 1.0;
+  double t[kMaxModes - 2][EP];
+#pragma unroll
+  for (int j = 0; j < kMaxModes - 2; ++j)
+#pragma unroll
+    for (int q = 0; q < EP; ++q) t[j][q] = 1.0;
   if (a.next_mode >= 0) {
     const int lo = a.mode < a.next_mode ? a.mode : a.next_mode;
     const int hi = a.mode < a.next_mode ? a.next_mode : a.mode;
@@ -868,16 +942,13 @@ __device__ __forceinline__ void fin_preload(const FinalizeArgs& a, FinPre<EP>& p
       int k = j;
       if (k >= lo) ++k;
       if (k >= hi) ++k;
-      const bool use = k < a.N;
-      const int kc = use ? k : 0;
-      double t[EP];
+      if (k < a.N) {  // uniform
 #pragma unroll
-      for (int q = 0; q < EP; ++q) {
-        const int e = tid + NTF * q;
-        t[q] = a.G[(int64_t)kc * RR + (e < RR ? e : 0)];
+        for (int q = 0; q < EP; ++q) {
+          const int e = tid + NTF * q;
+          t[j][q] = a.G[(int64_t)k * RR + (e < RR ? e : 0)];
+        }
       }
-#pragma unroll
-      for (int q = 0; q < EP; ++q) p.P[q] *= use ? t[q] : 1.0;
     }
   }
 #pragma unroll
@@ -893,6 +964,10 @@ __device__ __forceinline__ void fin_preload(const FinalizeArgs& a, FinPre<EP>& p
     p.alpha = a.alpha[0];
     p.it = *a.iter_counter;
   }
+#pragma unroll
+  for (int j = 0; j < kMaxModes - 2; ++j)
+#pragma unroll
+    for (int q = 0; q < EP; ++q) p.P[q] *= t[j][q];
 }
 
 // lambda, normalised Gram, S of the next mode, the raw Gram if asked, and the fit.
@@ -1105,7 +1180,8 @@ __device__ __forceinline__ void small_op(const A& a, int variant, int bx, int by
       default: mttv_lead_body<64, float>(a, bx); break;
     }
   } else if constexpr (KIND == K_UPDATE) {
-    update_reg_body<VAR>(a, bx);
+    if constexpr (VAR >= kUpdLane) update_lane_body<VAR - kUpdLane>(a, bx);
+    else update_reg_body<VAR>(a, bx);
   }
 }
 
@@ -1250,11 +1326,33 @@ static hipError_t record_or_launch(const Sink& sk, int kind, int variant, unsign
   return hipLaunchKernel(kernel, dim3(gx, gy), dim3(threads), args, lds, sk.st);
 }
 
-hipError_t mttv_trail_launch(const MttvArgs& a, const Sink& sk) {
+// Runs of J for a trailing multi-TTV: at least 256 j each, and no more groups than
+// two per CU. (Splitting costs one more launch, about 3 us; 512 j in one group take
+// about 10.)
+int mttv_trail_split(int64_t Ia, int64_t J, int R) {
+  const int64_t groups = (Ia + 63) / 64 * R;
+  int64_t nz = 512 / groups;
+  if (nz > J / 256) nz = J / 256;
+  return nz < 2 ? 1 : (int)nz;
+}
+
+hipError_t mttv_trail_launch(const MttvArgs& a0, const Sink& sk) {
+  MttvArgs a = a0;
   if (a.Ia <= 0 || a.R <= 0) return hipSuccess;
+  a.nz = a.part ? mttv_trail_split(a.Ia, a.J, a.R) : 1;
+  a.jz = (a.J + a.nz - 1) / a.nz;
   const void* k = a.t_f64 ? (const void*)mttv_trail_kernel<double> : (const void*)mttv_trail_kernel<float>;
-  return record_or_launch(sk, K_MTTV_TRAIL, a.t_f64 ? 1 : 0, (unsigned)((a.Ia + 63) / 64), (unsigned)a.R, 0, k, &a,
-                          sizeof(a));
+  hipError_t e = record_or_launch(sk, K_MTTV_TRAIL, a.t_f64 ? 1 : 0, (unsigned)((a.Ia + 63) / 64 * a.nz),
+                                  (unsigned)a.R, 0, k, &a, sizeof(a));
+  if (e != hipSuccess || a.nz == 1) return e;
+  ReduceArgs r{};
+  r.part = a.part;
+  r.T = a.out;
+  r.t_f64 = a.out_f64;
+  r.Mtot = r.Mpad = a.Ia;
+  r.RP = r.R = a.R;
+  r.nsplit = a.nz;
+  return pm_reduce_launch(r, sk);
 }
 
 hipError_t mttv_lead_launch(const MttvArgs& a, const Sink& sk) {
@@ -1286,6 +1384,15 @@ hipError_t update_launch(const UpdateArgs& a, const Sink& sk) {
   const unsigned g = (unsigned)((a.I + rpb - 1) / rpb);
   if (a.R <= 64) {
     const int rb = a.R <= 16 ? 16 : (a.R <= 32 ? 32 : 64);
+    // One lane per row from 4096 rows (R <= 16) or 8192 (R <= 32): below, the row's
+    // latency counts, and a wave per row has the shorter chain. us, wave / lane per
+    // row: R = 16, 4000 rows 6.4 / 6.9, 30012 rows 24 / 7.5; R = 32, 4000 rows 10.0 /
+    // 17.5, 8192 rows 18 / 17.5, 30012 rows 60 / 19. R > 32: a row does not fit a
+    // lane's registers.
+    if (a.R <= 32 && a.I >= (rb == 16 ? kUpdLaneRows : 2 * kUpdLaneRows)) {
+      const void* k = rb == 16 ? (const void*)update_lane_kernel<16> : (const void*)update_lane_kernel<32>;
+      return record_or_launch(sk, K_UPDATE, kUpdLane + rb, (unsigned)((a.I + NT - 1) / NT), 1, 0, k, &a, sizeof(a));
+    }
     const void* k = rb == 16 ? (const void*)update_reg_kernel<16>
                              : (rb == 32 ? (const void*)update_reg_kernel<32> : (const void*)update_reg_kernel<64>);
     return record_or_launch(sk, K_UPDATE, rb, g, 1, 0, k, &a, sizeof(a));
@@ -1342,6 +1449,8 @@ const void* small_batch_kernel_ptr(int kind, int variant) {
         case 16: return (const void*)small_items_kernel<K_UPDATE, 16>;
         case 32: return (const void*)small_items_kernel<K_UPDATE, 32>;
         case 64: return (const void*)small_items_kernel<K_UPDATE, 64>;
+        case kUpdLane + 16: return (const void*)small_items_kernel<K_UPDATE, kUpdLane + 16>;
+        case kUpdLane + 32: return (const void*)small_items_kernel<K_UPDATE, kUpdLane + 32>;
         default: return nullptr;
       }
     default: return nullptr;
@@ -1367,15 +1476,21 @@ size_t fin_batch_max_lds() {
   return m;
 }
 
-// Row chunks for the Gram: one group when the work is small (no second launch),
-// otherwise chunks of about I_chunk x R4^2 = 2^20 (R <= 64: 1024-thread groups
-// that compute only the upper triangle) or 2^19 (R > 64) products each, at most 64.
+// Row chunks for the Gram. R <= 64: a chunk's waves take about six groups of 16
+// rows each (fin_ns waves per column-block pair; twelve at R > 48, whose partials
+// are the largest to add up: 1344 x 50 in 14 chunks 8.6 + 14.4 us, in 7 12.5 + 8.4),
+// at most 32 chunks, one group without a second launch up to twice that; R > 64:
+// chunks of about 2^19 products, at most 64.
 int finalize_chunks(int64_t I, int R, int* rows_per_chunk) {
-  const int shift = R <= kSmallMaxR ? 20 : 19;
-  const int64_t R4 = R <= kSmallMaxR ? gram_r4(R) : R;
-  const int64_t work = I * R4 * R4;
-  int64_t chunks = (work + (1ll << shift) - 1) >> shift;
-  if (chunks > 64) chunks = 64;
+  int64_t chunks;
+  if (R <= kSmallMaxR) {
+    const int64_t rows = 16 * (R > 48 ? 12 : 6) * fin_ns(R);
+    chunks = I <= 2 * rows ? 1 : (I + rows - 1) / rows;
+    if (chunks > 32) chunks = 32;
+  } else {
+    chunks = (I * R * R + (1ll << 19) - 1) >> 19;
+    if (chunks > 64) chunks = 64;
+  }
   if (chunks > I) chunks = I;
   if (chunks < 1) chunks = 1;
   int64_t rpc = (I + chunks - 1) / chunks;

@@ -1,0 +1,83 @@
+"""Dispatch edges of the small kernels against the FP64 oracle: the update with
+one lane per row, the Gram's row chunks and column-block pairs, and trailing
+multi-TTVs over a long J."""
+
+import numpy as np
+import pytest
+
+import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("I", [4095, 4096, 8191, 8192, 9001])  # either side of the rule, a short last group
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 32])
+@pytest.mark.parametrize("update,sweeps,tol", [("hals", 1, 0.0), ("mu", 2, 0.0), ("hals", 30, 1e-7)])
+def test_update_of_many_rows(gpu_lib, I, R, update, sweeps, tol):
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case update rows={I} R={R} {update} {sweeps} {tol}", flush=True)
+    rng = np.random.default_rng(I + 7 * R + sweeps)
+    K = rng.random((R + 20, R))
+    S = K.T @ K
+    if R > 2 and update == "hals":
+        S[2, :] = S[:, 2] = 0.0  # a column that is zero in another mode
+    M = rng.random((I, R)) * np.abs(S).sum(0) * 0.6
+    M[3] = -M[3]
+    H = rng.random((I, R)).astype(np.float32)
+    lam = rng.random(R) + 0.5
+    lam_t, G, W = native.nls_solve(torch.from_numpy(np.ascontiguousarray(M.T)).cuda(), native.factor_to_device(H), I, R,
+                                   torch.from_numpy(S).cuda(), torch.from_numpy(lam).cuda(), update,
+                                   max_sweeps=sweeps, tol=tol)
+    ref = O.block_update(H.astype(np.float64) * lam, S, M, update, sweeps, tol)
+    # FP64 throughout: R steps of R products, 2^-53 each, times the condition of S (< 1e4)
+    assert np.max(np.abs(W.cpu().numpy().T - ref)) <= 1e-9 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("R", [1, 16, 17, 32, 33, 48, 49, 64])
+def test_gram_rows_and_chunks(gpu_lib, R):
+    """Rows that end inside a group of 16 or of 4, one chunk and several."""
+    from paper_1806_07985_amd import native
+    rng = np.random.default_rng(R)
+    for I in (1, 3, 15, 16, 17, 31, 33, 191, 193, 383, 385, 961, 3071, 3073, 50001):
+        print(f"case gram I={I} R={R}", flush=True)
+        H = (rng.random((I, R)) - 0.3).astype(np.float32)
+        G = native.gram(native.factor_to_device(H), I, R).cpu().numpy()
+        ref, size = O.gram(H.astype(np.float64)), O.gram(np.abs(H.astype(np.float64)))
+        # exact products of FP32 values, FP64 sums: I roundings of 2^-53 at most
+        assert np.all(np.abs(G - ref) <= 2.0 ** -53 * (I + 40) * size)
+        assert np.array_equal(G, G.T)
+
+
+@pytest.mark.parametrize("dims,R,split,dt", [((6, 5, 512), 3, 1, "f32"), ((6, 5, 511), 3, 1, "f32"),
+                                             ((9, 65, 1100), 5, 1, "f32"), ((4, 7, 40, 37), 33, 1, "f32"),
+                                             ((5, 700, 3, 2), 2, 2, "f32"), ((6, 5, 1100), 4, 1, "bf16")])
+def test_trailing_multi_ttv_over_long_j(gpu_lib, dims, R, split, dt):
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case trail dims={dims} R={R} split={split} {dt}", flush=True)
+    rng = np.random.default_rng(sum(dims) + R)
+    X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32)).to({"f32": torch.float32, "bf16": torch.bfloat16}[dt])
+    X64 = X.double().numpy().reshape(dims, order="F")
+    H = [rng.random((d, R)).astype(np.float32) for d in dims]
+    Hd = [native.factor_to_device(h) for h in H]
+    for n in range(len(dims)):
+        M = native.mttkrp(X.cuda(), list(dims), split, n, Hd, R).cpu().numpy().T
+        ref = O.mttkrp_direct(X64, [h.astype(np.float64) for h in H], n)
+        # positive data; the partial MTTKRP's own bound (1e-6 FP32, 2e-6 16-bit plus its FP32 temporaries)
+        assert np.all(np.abs(M - ref) <= 3e-6 * ref), float(np.max(np.abs(M - ref) / ref))
+    # the same plan alone and in a batch, bitwise (both split the sum alike)
+    out = []
+    for batched in (False, True):
+        Hb = [native.factor_to_device(h) for h in H]
+        plan = native.Plan(X.cuda(), list(dims), R, Hb, split=split)
+        if batched:
+            b = native.Batch()
+            b.add(plan)
+            b.run(3)
+            b.close()
+        else:
+            plan.run(3)
+        out.append(Hb)
+        plan.close()
+    assert all(torch.equal(a, b) for a, b in zip(*out))
