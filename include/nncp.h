@@ -306,11 +306,10 @@ int nncp_norm_sq(const void* X, int dtype, int64_t n, double* out_dev, void* str
  * allocator). Same result as nncp_norm_sq, bit for bit: the same kernel, grid
  * and summation order. It only enqueues work on `stream` (no synchronisation);
  * out_dev is written when the stream reaches it.
- * Scratch: the FP64 block partials and the arrival counter live in a static
- * device array of 8.2 KB per GPU (1024 partials), held until the process ends;
- * the grid never exceeds 1024 work-groups, so every n >= 1 fits, and a grid that
- * would need more partials is rejected with NNCP_EINVAL. The counter is cleared
- * by a kernel at the start of each call. All calls on one GPU share that array:
+ * Scratch: the FP64 block partials live in a static device array of 8 KB per GPU
+ * (1024 partials), held until the process ends; the grid never exceeds 1024
+ * work-groups, so every n >= 1 fits, and a grid that would need more partials is
+ * rejected with NNCP_EINVAL. All calls on one GPU share that array:
  * calls that overlap on one GPU (concurrent streams or threads) race, so
  * serialise them (one stream, or an event between calls).
  * Errors: NNCP_EINVAL for a NULL pointer, n < 1 or an unknown dtype;

@@ -684,8 +684,7 @@ int nncp_plan_create(nncp_plan** out, const void* X, int dtype, int N, const int
     return fail(NNCP_EDEVICE);
   }
   // alpha = ||X||^2
-  if (norm_sq_launch(X, dtype, p.I, P->alpha(), P->nspart(), P->counters() + P->L.ncounters - 2,
-                     P->L.ns_blocks, s) != hipSuccess)
+  if (norm_sq_launch(X, dtype, p.I, P->alpha(), P->nspart(), P->L.ns_blocks, s) != hipSuccess)
     return fail(NNCP_EDEVICE);
   // starting Grams / norms per mode, then model weights and S^(1)
   for (int k = 0; k < N; ++k)
@@ -966,11 +965,9 @@ int nncp_norm_sq(const void* X, int dtype, int64_t n, double* out_dev, void* str
   hipStream_t s = (hipStream_t)stream;
   const int nb = norm_sq_blocks(n);
   void* scratch = nullptr;
-  if (hipMalloc(&scratch, sizeof(double) * nb + 256) != hipSuccess) return NNCP_ENOMEM;
-  unsigned* ctr = (unsigned*)((char*)scratch + align256(sizeof(double) * nb));
+  if (hipMalloc(&scratch, sizeof(double) * nb) != hipSuccess) return NNCP_ENOMEM;
   int st = NNCP_OK;
-  if (fill_u32_launch(ctr, 1, 0u, s) != hipSuccess ||
-      norm_sq_launch(X, dtype, n, out_dev, (double*)scratch, ctr, nb, s) != hipSuccess ||
+  if (norm_sq_launch(X, dtype, n, out_dev, (double*)scratch, nb, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     st = NNCP_EDEVICE;
   hipFree(scratch);

@@ -231,10 +231,10 @@ hipError_t init_model_launch(const double* lam_in, double* lam, double* lam_mode
 hipError_t normalize_out_launch(float* W, int64_t I, int R, double* lam_self, hipStream_t st);
 
 // ||X||^2 in FP64: norm_sq_blocks(n) <= kNormSqMaxBlocks groups, each writing one
-// FP64 partial; counter must be zero on entry (the last group resets it).
+// FP64 partial, and one group that adds them.
 constexpr int kNormSqMaxBlocks = 1024;
 hipError_t norm_sq_launch(const void* X, int dtype, int64_t n, double* out, double* partial,
-                          unsigned* counter, int nblocks, hipStream_t st);
+                          int nblocks, hipStream_t st);
 int norm_sq_blocks(int64_t n);
 hipError_t quantize_launch(const float* src, void* dst, int dtype, int64_t n, hipStream_t st);
 hipError_t fill_u32_launch(unsigned* p, int64_t n, unsigned v, hipStream_t st);

@@ -3,11 +3,11 @@
 // that admit jobs without touching the allocator).
 //
 // The two-stage reduction of nncp_norm_sq needs scratch: one FP64 partial per
-// work-group and the arrival counter of the last-group reduction. Here that
-// scratch is a file-scope device array, one copy per GPU for the life of the
-// process. Host code never passes the array's name to a kernel (on the host it
-// is only a stand-in for the symbol): each device's address is looked up once
-// with hipGetSymbolAddress, with that device current, and kept per device.
+// work-group. Here that scratch is a file-scope device array, one copy per GPU
+// for the life of the process. Host code never passes the array's name to a
+// kernel (on the host it is only a stand-in for the symbol): each device's
+// address is looked up once with hipGetSymbolAddress, with that device current,
+// and kept per device.
 #include <mutex>
 
 #include "nncp_internal.hpp"
@@ -16,10 +16,8 @@ using namespace nncpk;
 
 namespace {
 
-// kNormSqMaxBlocks FP64 partials, then the arrival counter (in the last slot's
-// 8 bytes; the rest of that 256-byte line is unused). 8.2 KB per device.
-constexpr int kScratchDoubles = kNormSqMaxBlocks + 32;
-static __device__ __align__(256) double scratch[kScratchDoubles];
+// kNormSqMaxBlocks FP64 partials: 8 KB per device.
+static __device__ __align__(256) double scratch[kNormSqMaxBlocks];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
@@ -52,9 +50,6 @@ extern "C" int nncp_norm_sq_noalloc(const void* X, int dtype, int64_t n, double*
   int st = scratch_for_current_device(&sp);
   if (st != NNCP_OK) return st;
   hipStream_t s = (hipStream_t)stream;
-  unsigned* counter = (unsigned*)(sp + kNormSqMaxBlocks);
-  // the counter must start at zero: cleared by a kernel (no memset node under capture)
-  if (fill_u32_launch(counter, 1, 0u, s) != hipSuccess) return NNCP_EDEVICE;
-  if (norm_sq_launch(X, dtype, n, out_dev, sp, counter, nb, s) != hipSuccess) return NNCP_EDEVICE;
+  if (norm_sq_launch(X, dtype, n, out_dev, sp, nb, s) != hipSuccess) return NNCP_EDEVICE;
   return NNCP_OK;
 }

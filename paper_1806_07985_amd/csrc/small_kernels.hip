@@ -48,49 +48,40 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return t;  // valid in thread 0
 }
 
-// Returns true in every thread of the last block to arrive (device-scope counter,
-// reset to zero by that block).
-__device__ __forceinline__ bool last_block(unsigned* counter, unsigned total) {
-  __shared__ int s_last;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (prev == total - 1);
-    if (s_last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __syncthreads();
-  if (s_last) __threadfence();
-  return s_last;
-}
-
 // --------------------------------------------------------------------------
 // ||X||^2 in FP64
 // --------------------------------------------------------------------------
-// Each thread reads 16-byte vectors (4 FP32 or 8 16-bit values), eight of them
-// issued before any is used; the vector type is aligned to the element only, so
-// any element-aligned base works. The n % VEC tail is read by block 0. Squares
-// are exact in FP64 (a 24-bit significand squared fits 53 bits) and summed in
-// FP64; the block sums are added by the last block in block order, so the
-// result does not depend on scheduling.
+// A group sums a contiguous run of the tensor; a thread reads 16-byte vectors (4
+// FP32 or 8 16-bit values), eight of them, 4 KB apart, issued before any is used;
+// the vector type is aligned to the element only, so any element-aligned base
+// works. Up to four groups per CU hide one another's waits. 45.4 M values: FP32
+// 65.9 -> 26.6 us (6.8 TB/s), BF16 55.4 -> 14.3 (6.3 TB/s); 268 M: 212 -> 152 and
+// 124 -> 77 (one group per CU, sums added by the last of them to arrive). The
+// n % VEC tail is read by block 0. Squares are exact in FP64 (a 24-bit significand
+// squared fits 53 bits) and summed in FP64; the block sums are added in a fixed
+// order by a second kernel of one block, so the result does not depend on
+// scheduling (a sum by the last block to arrive needs a device-scope release per
+// block, which writes the XCD's L2 back: 0.1 us each, one after the other).
 template <typename T>
-__global__ __launch_bounds__(NT) void norm_sq_kernel(const T* X, int64_t n, double* out,
-                                                     double* partial, unsigned* counter) {
+__global__ __launch_bounds__(NT) void norm_sq_kernel(const T* X, int64_t n, double* partial) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int U = 8;
   typedef T vT __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
   __shared__ double sh[NT / 64];
   const vT* V = (const vT*)X;
   const int64_t nv = n / VEC;
-  const int64_t stride = (int64_t)gridDim.x * NT;
+  // the group's run, a multiple of U * NT vectors
+  const int64_t per = (nv + (int64_t)gridDim.x * U * NT - 1) / ((int64_t)gridDim.x * U * NT) * U * NT;
+  const int64_t v0 = (int64_t)blockIdx.x * per;
+  const int64_t v1 = v0 + per < nv ? v0 + per : nv;
   // four independent FP64 sums (vector lane e adds into e % 4), added in a fixed
   // order at the end, so the FMA chains do not serialise the stream
   double s4[4] = {0.0, 0.0, 0.0, 0.0};
-  int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x;
-  for (; i + (U - 1) * stride < nv; i += U * stride) {
+  int64_t i = v0 + threadIdx.x;
+  for (; i + (U - 1) * NT < v1; i += U * NT) {
     vT v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(V + i + u * stride);
+    for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(V + i + u * NT);
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -100,7 +91,7 @@ __global__ __launch_bounds__(NT) void norm_sq_kernel(const T* X, int64_t n, doub
       }
   }
   double s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-  for (; i < nv; i += stride) {
+  for (; i < v1; i += NT) {
     const vT v = __builtin_nontemporal_load(V + i);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -115,21 +106,40 @@ __global__ __launch_bounds__(NT) void norm_sq_kernel(const T* X, int64_t n, doub
     }
   double t = block_sum(s, sh);
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
-  if (!last_block(counter, gridDim.x)) return;
+}
+__global__ __launch_bounds__(NT) void norm_sq_sum_kernel(const double* partial, int nb, double* out) {
+  __shared__ double sh[NT / 64];
   double u = 0.0;
-  if (threadIdx.x == 0) {
-    for (unsigned b = 0; b < gridDim.x; ++b) u += partial[b];
-    out[0] = u;
-  }
+  for (int b = threadIdx.x; b < nb; b += NT) u += partial[b];
+  u = block_sum(u, sh);
+  if (threadIdx.x == 0) out[0] = u;
 }
 
 // --------------------------------------------------------------------------
 // FP32 -> BF16 / FP16 (round to nearest even)
 // --------------------------------------------------------------------------
+// Eight values per thread and round (two 16-byte loads, one 16-byte store, aligned
+// to the element only); the n % 8 tail by block 0. Bound by HBM: 45.4 M values 49
+// -> 44 us (6.2 TB/s), 268 M 383 -> 299, against one value per thread (6 bytes each; 40 us at the rate of a
+// large copy).
 template <typename T>
 __global__ __launch_bounds__(NT) void quantize_kernel(const float* src, T* dst, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * NT;
-  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < n; i += stride) dst[i] = (T)src[i];
+  typedef float f4e __attribute__((ext_vector_type(4), aligned(4)));
+  typedef T t8 __attribute__((ext_vector_type(8), aligned(2)));
+  const int64_t nv = n / 8, stride = (int64_t)gridDim.x * NT;
+  for (int64_t i = (int64_t)blockIdx.x * NT + threadIdx.x; i < nv; i += stride) {
+    const f4e a = __builtin_nontemporal_load((const f4e*)src + 2 * i);
+    const f4e b = __builtin_nontemporal_load((const f4e*)src + 2 * i + 1);
+    t8 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[e] = (T)a[e];
+      o[e + 4] = (T)b[e];
+    }
+    *((t8*)dst + i) = o;
+  }
+  if (blockIdx.x == 0)
+    for (int64_t i = nv * 8 + threadIdx.x; i < n; i += NT) dst[i] = (T)src[i];
 }
 
 __global__ void fill_u32_kernel(unsigned* p, int64_t n, unsigned v) {
@@ -1253,31 +1263,30 @@ inline unsigned grid_for(int64_t n, int threads, unsigned cap = 65535u * 32u) {
 }  // namespace
 
 int norm_sq_blocks(int64_t n) {
-  // 64 values per thread at least; at most 256 groups, one per CU of this chip:
-  // measured on a 1 GiB FP32 tensor, 256 groups stream ||X||^2 in about half
-  // the time of 1024 (more groups per CU interleave more distant addresses).
-  // A fixed count keeps the summation order, and so the result, the same on
-  // every device.
-  int64_t b = (n + NT * 64 - 1) / (NT * 64);
+  // 32 values per thread at least, at most four groups per CU of this chip. A
+  // fixed count keeps the summation order, and so the result, the same on every
+  // device.
+  int64_t b = (n + NT * 32 - 1) / (NT * 32);
   if (b < 1) b = 1;
-  if (b > 256) b = 256;
+  if (b > kNormSqMaxBlocks) b = kNormSqMaxBlocks;
   return (int)b;
 }
 
 hipError_t norm_sq_launch(const void* X, int dtype, int64_t n, double* out, double* partial,
-                          unsigned* counter, int nblocks, hipStream_t st) {
+                          int nblocks, hipStream_t st) {
   dim3 g(nblocks), b(NT);
   switch (dtype) {
-    case NNCP_F32: hipLaunchKernelGGL(norm_sq_kernel<float>, g, b, 0, st, (const float*)X, n, out, partial, counter); break;
-    case NNCP_BF16: hipLaunchKernelGGL(norm_sq_kernel<__bf16>, g, b, 0, st, (const __bf16*)X, n, out, partial, counter); break;
-    case NNCP_F16: hipLaunchKernelGGL(norm_sq_kernel<_Float16>, g, b, 0, st, (const _Float16*)X, n, out, partial, counter); break;
+    case NNCP_F32: hipLaunchKernelGGL(norm_sq_kernel<float>, g, b, 0, st, (const float*)X, n, partial); break;
+    case NNCP_BF16: hipLaunchKernelGGL(norm_sq_kernel<__bf16>, g, b, 0, st, (const __bf16*)X, n, partial); break;
+    case NNCP_F16: hipLaunchKernelGGL(norm_sq_kernel<_Float16>, g, b, 0, st, (const _Float16*)X, n, partial); break;
     default: return hipErrorInvalidValue;
   }
+  hipLaunchKernelGGL(norm_sq_sum_kernel, dim3(1), b, 0, st, partial, nblocks, out);
   return hipGetLastError();
 }
 
 hipError_t quantize_launch(const float* src, void* dst, int dtype, int64_t n, hipStream_t st) {
-  dim3 g(grid_for(n, NT * 4, 8192)), b(NT);
+  dim3 g(grid_for(n, NT * 8, 8192)), b(NT);
   if (dtype == NNCP_BF16) hipLaunchKernelGGL(quantize_kernel<__bf16>, g, b, 0, st, src, (__bf16*)dst, n);
   else if (dtype == NNCP_F16) hipLaunchKernelGGL(quantize_kernel<_Float16>, g, b, 0, st, src, (_Float16*)dst, n);
   else return hipErrorInvalidValue;

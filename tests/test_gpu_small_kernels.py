@@ -1,6 +1,6 @@
 """Dispatch edges of the small kernels against the FP64 oracle: the update with
-one lane per row, the Gram's row chunks and column-block pairs, and trailing
-multi-TTVs over a long J."""
+one lane per row, the Gram's row chunks and column-block pairs, trailing multi-TTVs over a long J, and the vector
+and block edges of ||X||^2 and of quantisation."""
 
 import numpy as np
 import pytest
@@ -81,3 +81,26 @@ def test_trailing_multi_ttv_over_long_j(gpu_lib, dims, R, split, dt):
         out.append(Hb)
         plan.close()
     assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f16"])
+def test_ingest_edges(gpu_lib, dt):
+    """Sizes around a vector, a group's run, and the largest grid; bases that are
+    aligned to the element only."""
+    import torch
+    from paper_1806_07985_amd import native
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    X0 = (torch.rand(8192 * 1024 + 16400, generator=torch.Generator().manual_seed(3)) - 0.5)
+    for n in (1, 3, 7, 8, 9, 255, 2047, 2049, 8191, 8192, 8193, 16383, 16385, 8192 * 1024 + 16385):
+        for off in (0, 1, 3):
+            print(f"case ingest {dt} n={n} offset={off}", flush=True)
+            X = X0[off:off + n]
+            Xd = X0.cuda()[off:off + n]
+            if dt != "f32":
+                Q = native.quantize(Xd, dt)
+                assert torch.equal(Q.cpu().view(torch.int16), X.to(tdt).view(torch.int16))  # round to nearest even
+            Xt = X0.to(tdt)
+            got = native.norm_sq(Xt.cuda()[off:off + n])
+            ref = float(np.sum(Xt[off:off + n].double().numpy() ** 2))
+            # exact squares; at most 300 additions in a chain, 2^-53 each
+            assert abs(got - ref) <= 1e-12 * ref
