@@ -1,5 +1,6 @@
 """Dispatch edges of the small kernels against the FP64 oracle: the update with
-one lane per row, the Gram's row chunks and column-block pairs, trailing multi-TTVs over a long J, and the vector
+one lane per row, the ranks at which a row's column steps are cut, the Gram's row
+chunks and column-block pairs, trailing multi-TTVs over a long J, and the vector
 and block edges of ||X||^2 and of quantisation."""
 
 import numpy as np
@@ -32,6 +33,29 @@ def test_update_of_many_rows(gpu_lib, I, R, update, sweeps, tol):
     ref = O.block_update(H.astype(np.float64) * lam, S, M, update, sweeps, tol)
     # FP64 throughout: R steps of R products, 2^-53 each, times the condition of S (< 1e4)
     assert np.max(np.abs(W.cpu().numpy().T - ref)) <= 1e-9 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("R", [1, 7, 8, 9, 16, 17, 24, 25, 32, 33, 49, 56, 57, 64])
+@pytest.mark.parametrize("sweeps,tol", [(1, 0.0), (30, 1e-7)])
+def test_update_rank_edges(gpu_lib, R, sweeps, tol):
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case update rank R={R} {sweeps} {tol}", flush=True)
+    rng = np.random.default_rng(R + sweeps)
+    I = 9
+    K = rng.random((R + 20, R))
+    S = K.T @ K
+    if R > 2:
+        S[R - 1, :] = S[:, R - 1] = 0.0
+    M = rng.random((I, R)) * np.abs(S).sum(0) * 0.6
+    M[3] = -M[3]
+    H = rng.random((I, R)).astype(np.float32)
+    lam = rng.random(R) + 0.5
+    _, _, W = native.nls_solve(torch.from_numpy(np.ascontiguousarray(M.T)).cuda(), native.factor_to_device(H), I, R,
+                               torch.from_numpy(S).cuda(), torch.from_numpy(lam).cuda(), "hals",
+                               max_sweeps=sweeps, tol=tol)
+    ref = O.block_update(H.astype(np.float64) * lam, S, M, "hals", sweeps, tol)
+    assert np.max(np.abs(W.cpu().numpy().T - ref)) <= 1e-9 * np.max(np.abs(ref))  # as above
 
 
 @pytest.mark.parametrize("R", [1, 16, 17, 32, 33, 48, 49, 64])
