@@ -63,8 +63,9 @@ typedef struct nncp_options {
   int phase_timers;   /* nonzero: time each phase with HIP events */
   double tol;         /* > 0: stop when |fit_k - fit_{k-1}| < tol (host check each iteration) */
   int pm_wg_kib;      /* partial MTTKRP: aim for at least this many KiB of the tensor per work-group
-                         (at most one work-group per CU); <= 0: 256. Depends only on the job, never on
-                         what else runs, so a job computes the same sums alone and in a batch. */
+                         (at most one work-group per CU); <= 0: 256, or, FP32 below 8 MiB, 1/32 of the
+                         tensor but at least 32. Depends only on the job, never on what else runs, so a
+                         job computes the same sums alone and in a batch. */
   int no_tree;         /* nonzero: compute every mode's MTTKRP directly from the tensor (one partial
                           MTTKRP + multi-TTVs per mode, N passes over X per iteration) instead of
                           through the dimension tree (two passes): the tree-less baseline */

@@ -26,9 +26,20 @@ static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // it keeps the split-K partial traffic small), and at least wg_kib KiB of X per
 // group, so a small tensor is not cut into tiles whose LDS staging outweighs
 // their share of X. The count depends on the job alone.
-static int64_t target_wgs(int64_t x_bytes, int wg_kib) {
+// Below 32 groups of the default 256 KiB (FP32, X under 8 MiB) a launch alone is
+// the latency of one group's walk, so X is cut into up to 32 groups of at least 32
+// KiB there: 60x50x40, R = 5 (480 KB, one group before): left / right 71 / 24 ->
+// 9.5 / 7.9 us; 100^3, R = 16: 86 -> 72 us per iteration. Finer groups for larger X
+// would serve a job alone (137x201x90, R = 40: 156 -> 104 us with 64 KiB) but cost
+// the same jobs in a batch, where other jobs fill the chip and each item restages
+// its factor (128 jobs, R = 33-64: 5.1 -> 6.4 ms with 64 KiB, 5.4 with 64 groups at
+// least; unchanged with 32), and a job's sums are the same alone and in a batch.
+// (16-bit sums stay in FP32 across a group's share of K, so their plans keep the
+// shares they have.)
+static int64_t target_wgs(int64_t x_bytes, int wg_kib, bool f32) {
   const int64_t per = (int64_t)(wg_kib > 0 ? wg_kib : 256) * 1024;
   int64_t t = x_bytes / per;
+  if (f32 && wg_kib <= 0 && t < 32) t = std::min<int64_t>(32, x_bytes / (32 * 1024));
   if (t < 1) t = 1;
   if (t > num_cus()) t = num_cus();
   return t;
@@ -84,7 +95,7 @@ static PmLaunch plan_impl(int side, int dtype, int64_t IL, int64_t IR, int I1, i
   // a tall 16-bit right node with J == 1 uses the specialised kernel (wider waves)
   L.j1 = (!f32 && side == 1 && Ktot / I1 == 1 && cdiv(Mtot, 4 * pm_16_wave_rows(1, L.nb, 1)) >= 64) ? 1 : 0;
   const int wave_rows = f32 ? pm_f32_wave_rows(side, L.nb, xs) : pm_16_wave_rows(side, L.nb, L.j1);
-  const int64_t target = target_wgs(IL * IR * (f32 ? 4 : 2), wg_kib);
+  const int64_t target = target_wgs(IL * IR * (f32 ? 4 : 2), wg_kib, f32);
 
   L.I1 = I1;
   L.J = Ktot / I1;

@@ -1,7 +1,7 @@
 """Dispatch edges of the small kernels against the FP64 oracle: the update with
 one lane per row, the ranks at which a row's column steps are cut, the Gram's row
-chunks and column-block pairs, trailing multi-TTVs over a long J, and the vector
-and block edges of ||X||^2 and of quantisation."""
+chunks and column-block pairs, trailing multi-TTVs over a long J, partial MTTKRPs of
+small tensors cut into small groups, and the vector and block edges of ||X||^2 and of quantisation."""
 
 import numpy as np
 import pytest
@@ -128,3 +128,21 @@ def test_ingest_edges(gpu_lib, dt):
             ref = float(np.sum(Xt[off:off + n].double().numpy() ** 2))
             # exact squares; at most 300 additions in a chain, 2^-53 each
             assert abs(got - ref) <= 1e-12 * ref
+
+
+@pytest.mark.parametrize("dims", [(5, 4, 3), (32, 16, 16), (33, 16, 16), (64, 32, 8), (7, 90, 160), (128, 128, 127),
+                                  (128, 128, 128), (512, 3, 700)])  # 240 B, 32 KiB, the ends of the rule at 8 MiB
+@pytest.mark.parametrize("R", [3, 20, 40])
+def test_small_tensors_in_small_groups(gpu_lib, dims, R):
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case small groups dims={dims} R={R}", flush=True)
+    rng = np.random.default_rng(sum(dims) + R)
+    X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32))
+    H = [rng.random((d, R)).astype(np.float32) for d in dims]
+    Hd = [native.factor_to_device(h) for h in H]
+    X64 = X.double().numpy().reshape(dims, order="F")
+    for n in range(3):
+        M = native.mttkrp(X.cuda(), list(dims), 1, n, Hd, R).cpu().numpy().T
+        ref = O.mttkrp_direct(X64, [h.astype(np.float64) for h in H], n)
+        assert np.all(np.abs(M - ref) <= 1e-6 * ref), float(np.max(np.abs(M - ref) / ref))  # positive data, FP32 products
