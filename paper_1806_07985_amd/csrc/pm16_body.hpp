@@ -194,16 +194,39 @@ __device__ __forceinline__ void reduce_waves(float (&accf)[NACC][4], double* lds
 // 31 bits (pm16_buf). The check is made per dword
 // and drops one that is half inside, so a tensor whose last element falls into
 // such a dword has it put in place when its step is computed (`put_last`).
+// LD_BUFH: a right node whose first extent is odd has its columns, or every other
+// j of them, start in the middle of a dword, and a 16-byte load from there costs the
+// address unit several passes (right node of F16 83x71x57x45, R = 24: 59 us; of
+// 82x71x57x45: 26). Such a lane loads the aligned 16 bytes that begin one element
+// earlier and the dword after them (the other lanes: none), and the step shifts
+// them into place: 31 us (35 if every lane loads the dword after). Every dword read
+// holds an element of the tensor, whose start is a dword's start.
 // LD_GEN: the rest (columns of hundreds of MB): a uniform check per step, masked
 // element loads in the steps that reach the tensor's end; their branches make the
 // compiler wait for every load in flight once per ring round.
-enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2 };
+enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2, LD_BUFH = 3 };
 template <int L, bool NTL>
 __device__ __forceinline__ u16v<L> buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   constexpr int aux = NTL ? kBufNt : 0;
   if constexpr (L == 8) return __builtin_bit_cast(u16v<8>, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, aux));
   else return __builtin_bit_cast(u16v<4>, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)off, 0, aux));
 }
+// Eight consecutive elements as loaded, and as the MFMA operand (sh: 16 if they
+// begin in the upper half of the first dword, else 0).
+template <int LD>
+struct Oct {
+  u16v<8> v;
+  __device__ __forceinline__ u4 get(unsigned) const { return __builtin_bit_cast(u4, v); }
+};
+template <>
+struct Oct<LD_BUFH> {
+  u4 v;
+  unsigned w;
+  __device__ __forceinline__ u4 get(unsigned sh) const {
+    return u4{__builtin_amdgcn_alignbit(v[1], v[0], sh), __builtin_amdgcn_alignbit(v[2], v[1], sh),
+              __builtin_amdgcn_alignbit(v[3], v[2], sh), __builtin_amdgcn_alignbit(w, v[3], sh)};
+  }
+};
 // v holds elements whose d-th and later lie past the tensor: if that cut a dword
 // in half (d odd), its inside half is the tensor's last element.
 template <int L>
@@ -454,7 +477,8 @@ template <int DT, int NB, bool J1, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   constexpr int RP = NB * 16;
   constexpr int MC = J1 ? right_mc16_j1(NB) : right_mc16(NB);
-  constexpr int D = J1 ? right_pf16_j1(NB) : right_pf16(NB);
+  constexpr bool BUF = LD == LD_BUF || LD == LD_BUFH;
+  constexpr int D = J1 ? (LD == LD_BUFH ? 2 : right_pf16_j1(NB)) : right_pf16(NB);
   constexpr int KS = 64;
   constexpr int NACC = MC * NB;
   constexpr int NTM = pm16_terms(DT);
@@ -511,15 +535,17 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   const int64_t IX = Mtot * Ktot;
   int64_t cwk = 0;
   uint32_t voff[MC];
-  const unsigned short xlast = LD == LD_BUF ? X[IX - 1] : 0;
+  const unsigned short xlast = BUF ? X[IX - 1] : 0;
+  // LD_BUFH (I1 odd, X on a dword): the lane's columns start in an upper half
+  const unsigned lodd = LD == LD_BUFH ? (unsigned)(li & Ktot & 1) : 0;
   auto set_tile = [&](int t) {
     const int64_t cw = (int64_t)(tile0 + t) * mtile + wm * 16 * MC;
     cwk = cw * Ktot;
 #pragma unroll
     for (int g = 0; g < MC; ++g) {
       const int64_t c = cw + 16 * g + li;
-      if constexpr (LD == LD_BUF)
-        voff[g] = c < Mtot ? (uint32_t)(((int64_t)(16 * g + li) * Ktot + 8 * lq) * 2) : kBufNone;
+      if constexpr (BUF)
+        voff[g] = c < Mtot ? (uint32_t)(((int64_t)(16 * g + li) * Ktot + 8 * lq - lodd) * 2) : kBufNone;
       else
         colp[g] = X + Ktot * (c < Mtot ? c : 0) + 8 * lq;
     }
@@ -538,7 +564,7 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
   int tl = sb - jcntL * S1L;
   int jl = jcntL + jrot;
   if (jl >= jn) jl -= jn;
-  auto load = [&](vT (&A)[MC][2]) {
+  auto load = [&](Oct<LD> (&A)[MC][2]) {
     const int i1s = (ib0 + stL) * a.i1blk;
     const int64_t lbase = (int64_t)a.I1 * (j0 + jl) + i1s + KS * tl;
     if constexpr (LD == LD_BUF) {
@@ -546,12 +572,26 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int g = 0; g < MC; ++g) A[g][h] = buf_load16<8, NTL>(rs, voff[g] + 64 * h);
+        for (int g = 0; g < MC; ++g) A[g][h].v = buf_load16<8, NTL>(rs, voff[g] + 64 * h);
+    } else if constexpr (LD == LD_BUFH) {
+      // lbase is odd with j (cwk, i1s and KS are even): the resource starts one
+      // element earlier then, and a lane of odd columns on the dword after that
+      const unsigned odd = (unsigned)((j0 + jl) & 1);
+      const __amdgpu_buffer_rsrc_t rs = buf_rsrc<2>(X + cwk + lbase - odd, IX - cwk - lbase + odd);
+      const uint32_t up = odd ? 4 * lodd : 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int g = 0; g < MC; ++g) {
+          A[g][h].v = __builtin_bit_cast(u4, buf_load16<8, NTL>(rs, voff[g] + up + 64 * h));
+          A[g][h].w = (unsigned)__builtin_amdgcn_raw_buffer_load_b32(
+              rs, (int)(lodd != odd ? voff[g] + up + 64 * h + 16 : kBufNone), 0, NTL ? kBufNt : 0);
+        }
     } else if (LD == LD_FAST || lbase <= vec_lim) {  // uniform
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int g = 0; g < MC; ++g) A[g][h] = tload<NTL>((const vT*)(colp[g] + lbase + 32 * h));
+        for (int g = 0; g < MC; ++g) A[g][h].v = tload<NTL>((const vT*)(colp[g] + lbase + 32 * h));
     } else {
       const int ilimL = a.I1 - i1s;
 #pragma unroll
@@ -571,7 +611,7 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
               v[e] = *p;
             }
           }
-          A[g][h] = v;
+          A[g][h].v = v;
         }
       }
     }
@@ -623,16 +663,26 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
       }
   };
   int stC = 0, S1C = S1L, jc = jl, tc = tl, jcntC = jcntL, tileC = 0, left = se - sb;
-  auto compute = [&](vT (&A)[MC][2]) {
+  auto compute = [&](Oct<LD> (&A)[MC][2]) {
     const int kk = KS * tc + 8 * lq;
-    if (LD == LD_BUF && (a.I1 & 1) && tc + 1 == S1C && j0 + jc + 1 == a.J && ib0 + stC + 1 == a.n_i1blk) {
+    const unsigned sh = 16 * (lodd ^ (unsigned)((j0 + jc) & 1));  // LD_BUFH only
+    u4 av[MC][2];
+#pragma unroll
+    for (int g = 0; g < MC; ++g)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) av[g][h] = A[g][h].get(sh);
+    if (BUF && (a.I1 & 1) && tc + 1 == S1C && j0 + jc + 1 == a.J && ib0 + stC + 1 == a.n_i1blk) {
       // the step with the end of the tensor's last column
       const int64_t cw = (int64_t)(tile0 + tileC) * mtile + wm * 16 * MC;
       const int d = a.I1 - (ib0 + stC) * a.i1blk - kk;
 #pragma unroll
       for (int g = 0; g < MC; ++g)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) put_last<8>(A[g][h], cw + 16 * g + li + 1 == Mtot ? d - 32 * h : 0, xlast);
+        for (int h = 0; h < 2; ++h) {
+          u16v<8> v = __builtin_bit_cast(u16v<8>, av[g][h]);
+          put_last<8>(v, cw + 16 * g + li + 1 == Mtot ? d - 32 * h : 0, xlast);
+          av[g][h] = __builtin_bit_cast(u4, v);
+        }
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -647,7 +697,7 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
         for (int g = 0; g < MC; ++g)
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb)
-            c32[g][nb] = T16<DT>::mfma(__builtin_bit_cast(u4, A[g][h]), B[t][nb], c32[g][nb]);
+            c32[g][nb] = T16<DT>::mfma(av[g][h], B[t][nb], c32[g][nb]);
     }
     --left;
     if (!J1 && (tc + 1 == S1C || left == 0)) {
@@ -693,7 +743,7 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
     }
   };
 
-  vT A[D][MC][2];
+  Oct<LD> A[D][MC][2];
   int s = sb;
 #pragma unroll
   for (int d = 0; d < D; ++d) load(A[d]);
@@ -777,6 +827,10 @@ const void* pick(int nb, bool batch) {
 
 template <int DT, int LD, bool MT>
 const void* pick_side(int side, int nb, int j1, bool batch) {
+  if constexpr (LD == LD_BUFH) {
+    if (side == 0) return nullptr;
+    return j1 ? pick<DT, 1, true, LD, MT>(nb, batch) : pick<DT, 1, false, LD, MT>(nb, batch);
+  }
   if (j1) return side == 1 ? pick<DT, 1, true, LD, MT>(nb, batch) : nullptr;
   return side == 0 ? pick<DT, 0, false, LD, MT>(nb, batch) : pick<DT, 1, false, LD, MT>(nb, batch);
 }
@@ -786,6 +840,7 @@ const void* pick_load(int side, int nb, int j1, int ld, bool batch) {
   switch (ld) {
     case LD_FAST: return pick_side<DT, LD_FAST, MT>(side, nb, j1, batch);
     case LD_BUF: return pick_side<DT, LD_BUF, MT>(side, nb, j1, batch);
+    case LD_BUFH: return pick_side<DT, LD_BUFH, MT>(side, nb, j1, batch);
     default: return pick_side<DT, LD_GEN, MT>(side, nb, j1, batch);
   }
 }

@@ -51,16 +51,28 @@ size_t pm_16_reduce_lds(int side, int nb, int wm) {
   return (size_t)wm * nacc * 4 * 64 * sizeof(double);
 }
 
-// Which loads a launch uses (pm16_body.hpp: 0 masked, 1 plain, 2 range-checked):
+// Which loads a launch uses (pm16_body.hpp: 0 masked, 1 plain, 2 range-checked, 3
+// range-checked from dword starts):
 // plain ones for a right node, or a left node whose columns start on cache lines,
 // if the shape allows them; range-checked without the streaming hint for the rest.
 // F16 83x71x57x45 R = 24 left node 34.9 -> 28.7 us, BF16 200x180x220 R = 32 right
 // node 39.9 -> 27.0, BF16 30012x1200x48 R = 10 right node 1361 -> 843 us against
 // the masked loads with the hint (1338 range-checked with it).
-static int load_form(const PmLaunch& L, int64_t IL, int I1) {
+// A right node of odd I_1 loads from dword starts (LD_BUFH) where the address unit is
+// what its waves wait for: F16 83x71x57x45 R = 24 59 -> 31 us, BF16 301x40000 R = 10 30
+// -> 19, 83x71x2565 R = 48 63 -> 45. Not where one wave is alone on its CU and waits
+// for its own loads (83x64x9, R = 5: 64 -> 89 us), and not with four column blocks
+// where most of a k-step is padding (15x20x40001 R = 40 80 -> 84, 31x5x40001 R = 48
+// 66 -> 61).
+static bool from_dwords(const PmLaunch& L, const void* X, int64_t IR, int I1) {
+  if (L.side != 1 || !(I1 & 1) || ((uintptr_t)X & 3) != 0) return false;
+  if (L.wm == 4 && IR <= pm_16_wave_rows(1, L.nb, L.j1)) return false;
+  return L.nb < 4 || I1 > 16;
+}
+static int load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
   const bool fast = pm16_fast(L.side, IL, I1, L.nb);
   if (fast && (L.side == 1 || IL % 64 == 0)) return 1;
-  if (pm16_buf(L.side, IL, L.nb, L.j1)) return 2;
+  if (pm16_buf(L.side, IL, L.nb, L.j1)) return from_dwords(L, X, IR, I1) ? 3 : 2;
   return fast ? 1 : 0;
 }
 
@@ -70,7 +82,7 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const bool bf = L.dtype == NNCP_BF16;
   PackArgs pa{a.krp.f[0], a.I1, a.I1pad, a.R, a.col0, RP, a.hpack, a.hscale};
   const int wm = a.wm;
-  const int ld = load_form(L, a.IL, a.I1);
+  const int ld = load_form(L, a.X, a.IL, a.IR, a.I1);
   const bool mt = L.mper > 1;
   // variant = j1*100000 + bf16*10000 + side*1000 + nb*100 + mt*10 + load form
   const int variant =

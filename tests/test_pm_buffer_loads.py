@@ -74,3 +74,30 @@ def test_ragged_16bit_tensor_between_nans(gpu_lib, dims, R, s, dt):
             ref = fn(X64, [h.astype(np.float64) for h in H], s).reshape(-1, R, order="F")
             # the 16-bit path's bound: 2e-6 of sum |x||k| (all positive here)
             assert np.all(np.abs(T - ref) <= 2e-6 * ref), (side, at, float(np.max(np.abs(T - ref) / ref)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dims,s", [((33, 9, 150), 1), ((83, 3, 131), 2), ((5, 41, 301), 2), ((33, 4, 200), 2),
+                                    ((33, 5, 200), 2), ((201, 90), 1), ((83, 71, 90), 2), ((129, 33001), 1),
+                                    ((129, 66000), 1), ((1, 129), 1), ((15, 3, 300), 2), ((17, 3, 300), 2),
+                                    ((257, 1, 3, 70), 2)])
+@pytest.mark.parametrize("R", [5, 20, 40])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_right_node_of_odd_extent_between_nans(gpu_lib, dims, s, R, dt):
+    """Columns that start in the middle of a dword: every one, or every other j."""
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case odd extents {dt} dims={dims} R={R} s={s}", flush=True)
+    rng = np.random.default_rng(sum(dims) + R + s)
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32)).to(tdt)
+    X[-1] = X[0] = 100.0
+    H = [rng.random((d, R)).astype(np.float32) for d in dims]
+    room = torch.full((X.numel() + 20011,), float("nan"), device="cuda", dtype=tdt)
+    Xd = room[10002:10002 + X.numel()]  # on a dword, NaN before and after
+    Xd.copy_(X)
+    T = native.partial_mttkrp(Xd, list(dims), s, 1, [native.factor_to_device(h) for h in H], R).cpu().numpy().T
+    ref = O.partial_mttkrp_right(X.double().numpy().reshape(dims, order="F"), [h.astype(np.float64) for h in H], s)
+    ref = ref.reshape(-1, R, order="F")
+    # the 16-bit path's bound: 2e-6 of sum |x||k| (all positive here)
+    assert np.all(np.abs(T - ref) <= 2e-6 * ref), float(np.max(np.abs(T - ref) / ref))
