@@ -41,6 +41,106 @@ namespace {
     }                                             \
   } while (0)
 
+// Scratch of a step entry point (nncp_mttkrp, nncp_nls_solve, ...): these calls
+// end with a synchronised stream, so their block is idle by then and the next call,
+// on whatever stream or thread, may have it. Up to two blocks of at most 64 MiB are
+// kept per device (a call for more allocates and frees its own): hipMalloc, and
+// hipFree's wait for the whole device, took longer than the kernels of a small call
+// (37x29x31x23x19 MTTKRP, R = 16: 98 -> 62 us a call; 400x300x200 partial MTTKRP, R = 96:
+// 158 -> 109; NLS of 1344 rows, R = 50: 150 -> 147). Kept blocks are given back
+// where an allocation of a plan or a call fails.
+struct Shelf {
+  struct Block {
+    void* p;
+    size_t size;
+  };
+  static constexpr int kDevices = 64, kBlocks = 2;
+  static constexpr size_t kMinBlock = 64 << 10, kMaxBlock = 64 << 20;
+  std::mutex mu;
+  Block at[kDevices][kBlocks] = {};
+
+  // smallest kept block of at least `bytes`, or none
+  Block get(int dev, size_t bytes) {
+    std::lock_guard<std::mutex> lk(mu);
+    Block* best = nullptr;
+    for (Block& b : at[dev])
+      if (b.p && b.size >= bytes && (!best || b.size < best->size)) best = &b;
+    if (!best) return Block{};
+    const Block r = *best;
+    *best = Block{};
+    return r;
+  }
+  // keeps b, in place of the smallest where all are taken; returns the block to free
+  Block put(int dev, Block b) {
+    std::lock_guard<std::mutex> lk(mu);
+    Block* least = &at[dev][0];
+    for (Block& k : at[dev])
+      if (k.size < least->size) least = &k;
+    if (least->p && least->size >= b.size) return b;
+    const Block r = *least;
+    *least = b;
+    return r;
+  }
+  // frees the current device's blocks; true if there were any
+  bool release(int dev) {
+    bool any = false;
+    if (dev >= 0 && dev < kDevices)
+      for (Block b; (b = get(dev, 1)).p; any = true) (void)hipFree(b.p);
+    return any;
+  }
+};
+Shelf g_shelf;
+
+int current_device() {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
+
+// hipMalloc that gives the kept blocks back before it fails.
+hipError_t device_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && g_shelf.release(current_device())) e = hipMalloc(p, bytes);
+  return e;
+}
+
+struct Scratch {
+  void* p = nullptr;
+  size_t size = 0;
+  int dev = -1;
+  Scratch() = default;
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  ~Scratch() {  // after an error: hipFree waits for what was launched
+    if (p) (void)hipFree(p);
+  }
+  bool take(size_t bytes, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    dev = current_device();
+    // (a stream under capture is refused as an allocation is)
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone || dev < 0 ||
+        dev >= Shelf::kDevices || bytes > Shelf::kMaxBlock) {
+      (void)hipGetLastError();
+      dev = -1;
+      return device_malloc(&p, bytes) == hipSuccess;
+    }
+    const Shelf::Block b = g_shelf.get(dev, bytes);
+    p = b.p;
+    size = b.size;
+    if (p) return true;
+    size = Shelf::kMinBlock;
+    while (size < bytes) size *= 2;
+    return device_malloc(&p, size) == hipSuccess;
+  }
+  // end of the call: waits for its stream, then the block is free for the next
+  int done(hipStream_t s) {
+    if (hipStreamSynchronize(s) != hipSuccess) return NNCP_EDEVICE;
+    void* f = dev >= 0 ? g_shelf.put(dev, Shelf::Block{p, size}).p : p;
+    p = nullptr;
+    if (f) (void)hipFree(f);
+    return NNCP_OK;
+  }
+};
+
 constexpr int kFitCap = 1024;
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -654,7 +754,7 @@ int nncp_plan_create(nncp_plan** out, const void* X, int dtype, int N, const int
     P->ws = (char*)workspace;
   } else {
     void* w = nullptr;
-    if (hipMalloc(&w, P->L.total) != hipSuccess) {
+    if (device_malloc(&w, P->L.total) != hipSuccess) {
       delete P;
       return NNCP_ENOMEM;
     }
@@ -964,27 +1064,20 @@ int nncp_norm_sq(const void* X, int dtype, int64_t n, double* out_dev, void* str
   if (!X || !out_dev || n < 1 || (dtype < 0 || dtype > 2)) return NNCP_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int nb = norm_sq_blocks(n);
-  void* scratch = nullptr;
-  if (hipMalloc(&scratch, sizeof(double) * nb) != hipSuccess) return NNCP_ENOMEM;
-  int st = NNCP_OK;
-  if (norm_sq_launch(X, dtype, n, out_dev, (double*)scratch, nb, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    st = NNCP_EDEVICE;
-  hipFree(scratch);
-  return st;
+  Scratch scratch;
+  if (!scratch.take(sizeof(double) * nb, s)) return NNCP_ENOMEM;
+  if (norm_sq_launch(X, dtype, n, out_dev, (double*)scratch.p, nb, s) != hipSuccess) return NNCP_EDEVICE;
+  return scratch.done(s);
 }
 
 // A throw-away plan-like context for the step entry points (no lambda scaling).
 struct StepCtx {
   nncp_plan P;
-  void* mem = nullptr;
-  ~StepCtx() {
-    if (mem) hipFree(mem);
-  }
+  Scratch mem;
 };
 
 static int step_ctx(StepCtx& c, const void* X, int dtype, int N, const int64_t* dims, int s, float* const* H,
-                    int R) {
+                    int R, hipStream_t hs) {
   int st = fill_problem(c.P.p, N, dims, R, dtype, NNCP_HALS, s);
   if (st != NNCP_OK) return st;
   c.P.L = make_layout(c.P.p);
@@ -993,24 +1086,23 @@ static int step_ctx(StepCtx& c, const void* X, int dtype, int N, const int64_t* 
     if (!H[k]) return NNCP_EINVAL;
     c.P.H[k] = H[k];
   }
-  if (hipMalloc(&c.mem, c.P.L.total) != hipSuccess) return NNCP_ENOMEM;
-  c.P.ws = (char*)c.mem;
-  if (fill_u32_launch(c.P.counters(), c.P.L.ncounters, 0u, nullptr) != hipSuccess) return NNCP_EDEVICE;
-  if (fill_u32_launch(c.P.zeros(), 64, 0u, nullptr) != hipSuccess) return NNCP_EDEVICE;
-  return NNCP_OK;
+  if (!c.mem.take(c.P.L.total, hs)) return NNCP_ENOMEM;
+  c.P.ws = (char*)c.mem.p;
+  if (hipDeviceSynchronize() != hipSuccess) return NNCP_EDEVICE;
+  // the zero block and the counters, with the two small fields between them
+  const int64_t words = (int64_t)(c.P.L.off_counters - c.P.L.off_zeros) / 4 + c.P.L.ncounters;
+  return fill_u32_launch(c.P.zeros(), words, 0u, hs) == hipSuccess ? NNCP_OK : NNCP_EDEVICE;
 }
 
 int nncp_partial_mttkrp(const void* X, int dtype, int N, const int64_t* dims, int s, int side,
                         float* const* H, int R, double* T, void* stream) {
   if (!X || !H || !T || (side != 0 && side != 1) || s < 1) return NNCP_EINVAL;
   StepCtx c;
-  int st = step_ctx(c, X, dtype, N, dims, s, H, R);
-  if (st != NNCP_OK) return st;
   hipStream_t hs = (hipStream_t)stream;
-  if (hipDeviceSynchronize() != hipSuccess) return NNCP_EDEVICE;
+  int st = step_ctx(c, X, dtype, N, dims, s, H, R, hs);
+  if (st != NNCP_OK) return st;
   if (run_pm(&c.P, side, T, 1, X, false, hs) != hipSuccess) return NNCP_EDEVICE;
-  if (hipStreamSynchronize(hs) != hipSuccess) return NNCP_EDEVICE;
-  return NNCP_OK;
+  return c.mem.done(hs);
 }
 
 int nncp_mttv(const double* T, int nm, const int64_t* node_dims, int kind, float* const* Hf, int R,
@@ -1055,10 +1147,9 @@ int nncp_mttkrp(const void* X, int dtype, int N, const int64_t* dims, int s, int
                 double* M, void* stream) {
   if (!X || !H || !M || s < 1 || n < 0 || n >= N) return NNCP_EINVAL;
   StepCtx c;
-  int st = step_ctx(c, X, dtype, N, dims, s, H, R);
-  if (st != NNCP_OK) return st;
   hipStream_t hs = (hipStream_t)stream;
-  if (hipDeviceSynchronize() != hipSuccess) return NNCP_EDEVICE;
+  int st = step_ctx(c, X, dtype, N, dims, s, H, R, hs);
+  if (st != NNCP_OK) return st;
   // the schedules of n's half from its first mode up to n: every node on the
   // path to leaf n is computed (with the given factors) by the time n's runs
   const Problem& p = c.P.p;
@@ -1070,7 +1161,7 @@ int nncp_mttkrp(const void* X, int dtype, int N, const int64_t* dims, int s, int
   if ((m_f64 ? copy_f64_launch(M, (const double*)Mp, cnt, hs) : widen_f32_launch(M, (const float*)Mp, cnt, hs)) !=
       hipSuccess)
     return NNCP_EDEVICE;
-  return hipStreamSynchronize(hs) == hipSuccess ? NNCP_OK : NNCP_EDEVICE;
+  return c.mem.done(hs);
 }
 
 int nncp_gram(const float* H, int64_t I, int R, double* G, void* stream) {
@@ -1081,8 +1172,9 @@ int nncp_gram(const float* H, int64_t I, int R, double* G, void* stream) {
   const size_t RR = (size_t)R * R;
   size_t bytes = align256(sizeof(double) * chunks * (RR + 1)) + align256(sizeof(double) * RR) +
                  align256(sizeof(double) * R) * 2 + 256;
-  char* mem = nullptr;
-  if (hipMalloc(&mem, bytes) != hipSuccess) return NNCP_ENOMEM;
+  Scratch scratch;
+  if (!scratch.take(bytes, hs)) return NNCP_ENOMEM;
+  char* mem = (char*)scratch.p;
   size_t o = 0;
   double* part = (double*)(mem + o);
   o += align256(sizeof(double) * chunks * (RR + 1));
@@ -1105,10 +1197,8 @@ int nncp_gram(const float* H, int64_t I, int R, double* G, void* stream) {
   f.partial = part;
   f.nchunks = chunks;
   f.rows_per_chunk = rpc;
-  int st = NNCP_OK;
-  if (finalize_launch(f, hs) != hipSuccess || hipStreamSynchronize(hs) != hipSuccess) st = NNCP_EDEVICE;
-  hipFree(mem);
-  return st;
+  if (finalize_launch(f, hs) != hipSuccess) return NNCP_EDEVICE;
+  return scratch.done(hs);
 }
 
 int nncp_nls_update(const double* M, float* H, int64_t I, int R, const double* S, double* lambda, int update,
@@ -1127,11 +1217,11 @@ int nncp_nls_solve(const double* M, float* H, int64_t I, int R, const double* S,
   const int chunks = finalize_chunks(I, R, &rpc);
   const size_t RR = (size_t)R * R;
   size_t bytes = align256(sizeof(double) * chunks * (RR + 1)) + align256(sizeof(double) * R) * 2 + 256;
-  char* mem = nullptr;
-  if (hipMalloc(&mem, bytes) != hipSuccess) return NNCP_ENOMEM;
+  Scratch scratch;
+  if (!scratch.take(bytes, hs)) return NNCP_ENOMEM;
+  char* mem = (char*)scratch.p;
   double* part = (double*)mem;
   double* ones = (double*)(mem + align256(sizeof(double) * chunks * (RR + 1)));
-  int st = NNCP_OK;
   UpdateArgs u{};
   u.M = M;
   u.m_f64 = 1;
@@ -1160,10 +1250,9 @@ int nncp_nls_solve(const double* M, float* H, int64_t I, int R, const double* S,
   f.rows_per_chunk = rpc;
   if (fill_f64_launch(ones, R, 1.0, hs) != hipSuccess ||
       update_launch(u, hs) != hipSuccess || finalize_launch(f, hs) != hipSuccess ||
-      normalize_out_launch(H, I, R, lambda, hs) != hipSuccess || hipStreamSynchronize(hs) != hipSuccess)
-    st = NNCP_EDEVICE;
-  hipFree(mem);
-  return st;
+      normalize_out_launch(H, I, R, lambda, hs) != hipSuccess)
+    return NNCP_EDEVICE;
+  return scratch.done(hs);
 }
 
 }  // extern "C"

@@ -146,3 +146,43 @@ def test_small_tensors_in_small_groups(gpu_lib, dims, R):
         M = native.mttkrp(X.cuda(), list(dims), 1, n, Hd, R).cpu().numpy().T
         ref = O.mttkrp_direct(X64, [h.astype(np.float64) for h in H], n)
         assert np.all(np.abs(M - ref) <= 1e-6 * ref), float(np.max(np.abs(M - ref) / ref))  # positive data, FP32 products
+
+
+def test_step_calls_share_scratch_safely(gpu_lib):
+    """Threads on their own streams, calls of growing and shrinking sizes: every
+    result equals the one computed alone (the calls are deterministic)."""
+    import threading
+    import torch
+    from paper_1806_07985_amd import native
+    rng = np.random.default_rng(5)
+    jobs = []
+    for i, (dims, R) in enumerate([((9, 8, 7), 3), ((60, 50, 40), 20), ((200, 150, 130), 64), ((31, 2, 900), 48)]):
+        X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32)).cuda()
+        H = [native.factor_to_device(rng.random((d, R)).astype(np.float32)) for d in dims]
+        jobs.append((X, list(dims), R, H))
+
+    def work(j):
+        X, dims, R, H = jobs[j]
+        T = [native.partial_mttkrp(X, dims, 1, side, H, R) for side in (0, 1)]
+        M = [native.mttkrp(X, dims, 1, n, H, R) for n in range(3)]
+        return T + M + [native.gram(H[0], dims[0], R)], native.norm_sq(X)
+
+    alone = [work(j) for j in range(len(jobs))]
+    torch.cuda.synchronize()
+    bad = []
+
+    def run(t):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for k in range(6):
+                j = (t + k) % len(jobs)
+                out, ns = work(j)
+                torch.cuda.current_stream().synchronize()
+                if ns != alone[j][1] or not all(torch.equal(a, b) for a, b in zip(out, alone[j][0])):
+                    bad.append((t, k, j))
+
+    threads = [threading.Thread(target=run, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
