@@ -1345,13 +1345,15 @@ static hipError_t record_or_launch(const Sink& sk, int kind, int variant, unsign
   return hipLaunchKernel(kernel, dim3(gx, gy), dim3(threads), args, lds, sk.st);
 }
 
-// Runs of J for a trailing multi-TTV: at least 256 j each, and no more groups than
-// two per CU. (Splitting costs one more launch, about 3 us; 512 j in one group take
-// about 10.)
+// Runs of J for a trailing multi-TTV: at least 128 j each, and no more groups than
+// two per CU; none below 384 j. (Splitting costs one more launch, about 3 us; a
+// group takes about 30 ns per j: 437 j, 16 groups, 14.5 us in one run,
+// 7.8 + 3.8 in three.)
 int mttv_trail_split(int64_t Ia, int64_t J, int R) {
+  if (J < 384) return 1;
   const int64_t groups = (Ia + 63) / 64 * R;
   int64_t nz = 512 / groups;
-  if (nz > J / 256) nz = J / 256;
+  if (nz > J / 128) nz = J / 128;
   return nz < 2 ? 1 : (int)nz;
 }
 

@@ -75,7 +75,9 @@ def test_gram_rows_and_chunks(gpu_lib, R):
 
 @pytest.mark.parametrize("dims,R,split,dt", [((6, 5, 512), 3, 1, "f32"), ((6, 5, 511), 3, 1, "f32"),
                                              ((9, 65, 1100), 5, 1, "f32"), ((4, 7, 40, 37), 33, 1, "f32"),
-                                             ((5, 700, 3, 2), 2, 2, "f32"), ((6, 5, 1100), 4, 1, "bf16")])
+                                             ((5, 700, 3, 2), 2, 2, "f32"), ((6, 5, 1100), 4, 1, "bf16"),
+                                             ((6, 5, 383), 3, 1, "f32"), ((6, 5, 384), 3, 1, "f32"),
+                                             ((4, 70, 437), 16, 1, "f32")])
 def test_trailing_multi_ttv_over_long_j(gpu_lib, dims, R, split, dt):
     import torch
     from paper_1806_07985_amd import native
