@@ -114,16 +114,14 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
     }
     return sink_record(sk, pm);
   }
-  if (a.sctab) {
-    hipError_t e = pm_scale_table_launch(L, a, sk.st);
-    if (e != hipSuccess) return e;
-  }
   {
-    void* pargs[] = {(void*)&pa};
+    PmArgs sa = a;
+    int64_t n = a.sctab ? L.J * RP : 0;
+    void* pargs[] = {(void*)&pa, (void*)&sa, (void*)&n};
     // one group per column: 1024 threads for a long one (I_1 = 30012: 52 us with 256)
     const int pt = a.I1pad > 2048 ? 1024 : 256;
     hipError_t e = hipLaunchKernel(bf ? pm16_pack_kernel<NNCP_BF16>(false, pt) : pm16_pack_kernel<NNCP_F16>(false, pt),
-                                   dim3(RP), dim3(pt), pargs, 0, sk.st);
+                                   dim3((unsigned)(RP + (n + pt - 1) / pt)), dim3(pt), pargs, 0, sk.st);
     if (e != hipSuccess) return e;
   }
   allow_big_lds(k);

@@ -61,6 +61,18 @@ __device__ __forceinline__ double krp_scale_entry(const KrpDesc& krp, uint32_t j
   return p;
 }
 
+// The scale table of a launch: sctab[j * RP + r] = Krest(j, col0 + r) times
+// the column's 1/lambda product (0 for r >= R), j < J. The same function of
+// (j, column) the work-groups otherwise evaluate themselves.
+template <int NTH>
+__device__ __forceinline__ void scale_table_block(const PmArgs& a, int RP, int64_t n, int64_t blk) {
+  const int64_t e = blk * NTH + threadIdx.x;
+  if (e >= n) return;
+  const int64_t j = e / RP;
+  const int r = (int)(e - j * RP);
+  a.sctab[e] = r < a.R ? krp_scale_entry(a.krp, (uint32_t)j, a.col0 + r) : 0.0;
+}
+
 // Buffer loads: a wave-uniform resource starts at `p` and holds `rem` elements of
 // ESZ bytes; dwords at or past its end read zero (checked dword by dword), and a
 // lane whose byte offset is kBufNone reads zero without touching memory. Offsets

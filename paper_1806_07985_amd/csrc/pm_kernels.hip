@@ -306,18 +306,8 @@ __global__ __launch_bounds__(NT, 2) void pm_f32_xs_items(const BItem* __restrict
   pm_walk_items(items, grp, ops, [](const PmArgs& a, int bx, int by) { pm_right_f32_xs_body<NB, xs_pf(NB), MT>(a, bx, by); });
 }
 
-// The scale table of a launch: sctab[j * RP + r] = Krest(j, col0 + r) times
-// the column's 1/lambda product (0 for r >= R), j < J. The same function of
-// (j, column) the work-groups otherwise evaluate themselves.
-__device__ __forceinline__ void scale_table_block(const PmArgs& a, int RP, int64_t n, int64_t blk) {
-  const int64_t e = blk * NT + threadIdx.x;
-  if (e >= n) return;
-  const int64_t j = e / RP;
-  const int r = (int)(e - j * RP);
-  a.sctab[e] = r < a.R ? krp_scale_entry(a.krp, (uint32_t)j, a.col0 + r) : 0.0;
-}
 __global__ __launch_bounds__(NT) void pm_scale_table_kernel(PmArgs a, int RP, int64_t n) {
-  scale_table_block(a, RP, n, blockIdx.x);
+  scale_table_block<NT>(a, RP, n, blockIdx.x);
 }
 // Batched form: an item runs `coarse` consecutive blocks of one recorded table.
 __global__ __launch_bounds__(NT) void pm_scale_table_items(const BItem* __restrict__ items,
@@ -333,7 +323,7 @@ __global__ __launch_bounds__(NT) void pm_scale_table_items(const BItem* __restri
     const int64_t tot = a.J * RP;
     for (unsigned c = 0; c < op.coarse; ++c) {
       const int64_t b = (int64_t)it.bx * op.coarse + c;
-      if (b < (int64_t)op.gx) scale_table_block(a, RP, tot, b);
+      if (b < (int64_t)op.gx) scale_table_block<NT>(a, RP, tot, b);
     }
   }
 }

@@ -1,7 +1,8 @@
 """Dispatch edges of the small kernels against the FP64 oracle: the update with
 one lane per row, the ranks at which a row's column steps are cut, the Gram's row
 chunks and column-block pairs, trailing multi-TTVs over a long J, partial MTTKRPs of
-small tensors cut into small groups, and the vector and block edges of ||X||^2 and of quantisation."""
+small tensors cut into small groups, the 16-bit pack and scale table of one launch,
+and the vector and block edges of ||X||^2 and of quantisation."""
 
 import numpy as np
 import pytest
@@ -188,3 +189,24 @@ def test_step_calls_share_scratch_safely(gpu_lib):
     for t in threads:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("dims,s,side", [((3, 2100, 5), 1, 0), ((2049, 3, 7), 2, 1), ((3, 2048, 70), 1, 0),
+                                         ((9, 8, 7), 1, 0), ((9, 16, 16), 1, 0), ((9, 16, 17, 2), 1, 0)])
+@pytest.mark.parametrize("R", [1, 16, 33])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+def test_pack_and_scale_table(gpu_lib, dims, s, side, R, dt):
+    """Either size of group (first contracted extents around 2048), tables that end
+    inside a group and on its end."""
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case pack {dt} dims={dims} R={R} s={s} side={side}", flush=True)
+    rng = np.random.default_rng(sum(dims) + R)
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    X = torch.from_numpy(rng.random(int(np.prod(dims))).astype(np.float32)).to(tdt)
+    H = [rng.random((d, R)).astype(np.float32) for d in dims]
+    T = native.partial_mttkrp(X.cuda(), list(dims), s, side, [native.factor_to_device(h) for h in H], R).cpu().numpy().T
+    fn = O.partial_mttkrp_left if side == 0 else O.partial_mttkrp_right
+    ref = fn(X.double().numpy().reshape(dims, order="F"), [h.astype(np.float64) for h in H], s).reshape(-1, R, order="F")
+    # the 16-bit path's bound: 2e-6 of sum |x||k| (all positive here)
+    assert np.all(np.abs(T - ref) <= 2e-6 * ref), float(np.max(np.abs(T - ref) / ref))
