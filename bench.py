@@ -7,7 +7,7 @@ This is one processor's share of the paper's 4-way weak-scaling experiment.
 
 A "step" is one outer iteration of the whole hot path (both partial MTTKRPs,
 all multi-TTVs, the FP64 Gram/Hadamard builds, the factor updates and the
-FP64 fit), replayed from a HIP graph; the tensor is resident in HBM before
+FP64 fit), its kernels launched one by one; the tensor is resident in HBM before
 timing starts. Prints one JSON line.
 """
 
@@ -185,7 +185,7 @@ def _lowprec_study(dev, iters, seconds_note=None):
         Xd = X32 if dt == "f32" else native.quantize(X32, dt)
         Hd = [native.factor_to_device(h, device=dev) for h in H0]
         plan = native.Plan(Xd, list(dims), R, Hd, update="hals", split=s)
-        f0 = plan.run(1)                       # first replay builds the graph
+        f0 = plan.run(1)                       # untimed: loads the kernels
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         fits = plan.run(iters - 1)
@@ -251,7 +251,7 @@ def _batch_study(dev, n_jobs, iters, wg_kib=0):
     t_batch = time.perf_counter() - t0
     st = batch.stats()
     alone = plans(graph=True)
-    for p_, _ in alone:                  # first run of each plan builds its graph: one iteration
+    for p_, _ in alone:                  # untimed, as the batch's first tick: one iteration
         p_.run(1)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -521,7 +521,7 @@ def main(argv=None):
     ms_tree = plan.time_mttkrp(10)
     tree_bytes = rt["left_bytes"] + rt["right_bytes"] + rt["mttv_bytes"]
 
-    # phase breakdown (events between kernels, no graph)
+    # phase breakdown (events between kernels)
     Hp = [native.factor_to_device(h, device=dev) for h in H0]
     pplan = native.Plan(Xd, dims, R, Hp, update=args.update, split=s, graph=False, phase_timers=True)
     pplan.run(3)
