@@ -165,6 +165,29 @@ struct TNode {
   size_t off = 0;       // its offset
 };
 
+// A partial MTTKRP's launches, one per chunk of kPmMaxCols columns. Each has a plan
+// of its own: a last chunk of fewer column blocks takes wider tiles, so it can be
+// split over K where the first is not, and may need the most scratch of all.
+struct PmChunks {
+  int n = 0;
+  PmLaunch at[(kMaxRank + kPmMaxCols - 1) / kPmMaxCols];
+};
+
+// Scratch that the launches of a plan share, one after the other.
+struct PmNeed {
+  size_t partial = 0, pack = 0, table = 0;  // doubles, bytes, doubles
+  void add(const PmChunks& c) {
+    for (int i = 0; i < c.n; ++i) {
+      partial = std::max(partial, c.at[i].partial_doubles);
+      pack = std::max(pack, c.at[i].pack_bytes);
+      table = std::max(table, pm_sctab_doubles(c.at[i]));
+    }
+  }
+  bool covers(const PmLaunch& l) const {
+    return l.partial_doubles <= partial && l.pack_bytes <= pack && pm_sctab_doubles(l) <= table;
+  }
+};
+
 struct Layout {
   size_t off_zeros, off_alpha, off_iter, off_counters, off_lam, off_lammodel, off_lamin, off_G, off_S, off_fit,
       off_finpart, off_pmpart, off_hpack, off_sctab, off_nspart, off_M, total;
@@ -177,11 +200,12 @@ struct Layout {
   TNode tn[2 * kMaxModes];
   int nsched[kMaxModes];
   int sched[kMaxModes][kMaxModes];
-  PmLaunch pmL[2];
+  PmChunks pmL[2];
+  PmNeed need;
   // without the dimension tree (ablation): per mode, the side and split of the
   // partial MTTKRP that computes it from X, and two temporaries
   int dside[kMaxModes], dsplit[kMaxModes];
-  PmLaunch dpm[kMaxModes];
+  PmChunks dpm[kMaxModes];
   size_t off_dtA, off_dtB;
   int ns_blocks;
 };
@@ -301,6 +325,15 @@ void build_tree(const Problem& p, Layout& L) {
   }
 }
 
+PmChunks pm_chunks(const Problem& p, int side, int s) {
+  PmChunks c;
+  const int64_t IL = prod_range(p, 0, s - 1), IR = p.I / IL;
+  for (int c0 = 0; c0 < p.R; c0 += kPmMaxCols)
+    c.at[c.n++] = pm_plan(side, p.dtype, IL, IR, (int)(side == 0 ? p.dims[s] : p.dims[0]),
+                          std::min(kPmMaxCols, p.R - c0), p.wg_kib);
+  return c;
+}
+
 Layout make_layout(const Problem& p) {
   Layout L{};
   const int N = p.N, R = p.R, RR = R * R;
@@ -310,15 +343,45 @@ Layout make_layout(const Problem& p) {
     o = align256(o + bytes);
     return at;
   };
-  L.pmL[0] = pm_plan(0, p.dtype, p.IL, p.IR, (int)p.dims[p.s], R, p.wg_kib);
-  L.pmL[1] = pm_plan(1, p.dtype, p.IL, p.IR, (int)p.dims[0], R, p.wg_kib);
+  // the launches, and the scratch that they share: partial sums (of the partial
+  // MTTKRPs, and of trailing multi-TTVs over a long J), the packed first factor and
+  // the scale table
+  build_tree(p, L);
+  auto trail = [&](int64_t rows, int64_t J) {
+    const int nz = mttv_trail_split(rows, J, R);
+    if (nz > 1) L.need.partial = std::max(L.need.partial, (size_t)nz * (size_t)rows * R);
+  };
+  for (int side = 0; side < 2; ++side) {
+    L.pmL[side] = pm_chunks(p, side, p.s);
+    L.need.add(L.pmL[side]);
+  }
+  for (int i = 0; i < L.ntn; ++i)
+    if (L.tn[i].kind == T_TRAIL) trail(L.tn[i].rows, prod_range(p, L.tn[i].b + 1, L.tn[L.tn[i].parent].b));
+  int64_t tmax = 1;
+  if (p.no_tree) {
+    // mode n from X directly: left with split n+1 (temporary over modes 1..n, then
+    // leading multi-TTVs down to mode n) or right with split n (temporary over
+    // modes n..N, then one trailing multi-TTV), whichever temporary is smaller
+    for (int n = 0; n < N; ++n) {
+      const int64_t tl = n <= N - 2 ? prod_range(p, 0, n) : INT64_MAX;
+      const int64_t tr = n >= 1 ? prod_range(p, n, N - 1) : INT64_MAX;
+      L.dside[n] = tl <= tr ? 0 : 1;
+      L.dsplit[n] = L.dside[n] == 0 ? n + 1 : n;
+      L.dpm[n] = pm_chunks(p, L.dside[n], L.dsplit[n]);
+      L.need.add(L.dpm[n]);
+      tmax = std::max(tmax, std::min(tl, tr));
+      if (L.dside[n] == 1 && n < N - 1) trail(p.dims[n], prod_range(p, n + 1, N - 1));
+    }
+  }
   int maxchunks = 1;
+  int64_t maxI = 0;
   for (int k = 0; k < N; ++k) {
     int rpc;
     maxchunks = std::max(maxchunks, finalize_chunks(p.dims[k], R, &rpc));
+    maxI = std::max(maxI, p.dims[k]);
   }
   L.ns_blocks = norm_sq_blocks(p.I);
-  L.ncounters = std::max(L.pmL[0].ncounters, L.pmL[1].ncounters) + 4;
+  L.ncounters = std::max(L.pmL[0].at[0].ncounters, L.pmL[1].at[0].ncounters) + 4;
   L.off_zeros = take(256);
   L.off_alpha = take(sizeof(double));
   L.off_iter = take(sizeof(int));
@@ -330,66 +393,19 @@ Layout make_layout(const Problem& p) {
   L.off_S = take(sizeof(double) * N * RR);
   L.off_fit = take(sizeof(double) * kFitCap);
   L.off_finpart = take(sizeof(double) * (size_t)maxchunks * (RR + 1));
-  // split sums: of the partial MTTKRPs, and of trailing multi-TTVs over a long J
-  // (used one after the other)
-  build_tree(p, L);
-  size_t part0 = std::max(L.pmL[0].partial_doubles, L.pmL[1].partial_doubles);
-  for (int i = 0; i < L.ntn; ++i)
-    if (L.tn[i].kind == T_TRAIL) {
-      const int64_t J = prod_range(p, L.tn[i].b + 1, L.tn[L.tn[i].parent].b);
-      const int nz = mttv_trail_split(L.tn[i].rows, J, R);
-      if (nz > 1) part0 = std::max(part0, (size_t)nz * (size_t)L.tn[i].rows * R);
-    }
-  L.off_pmpart = take(sizeof(double) * part0);
-  L.off_hpack = take(std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes));
-  // the scale table of a partial MTTKRP (the largest root launch)
-  size_t tab = std::max(pm_sctab_doubles(L.pmL[0]), pm_sctab_doubles(L.pmL[1]));
-  L.off_sctab = take(sizeof(double) * tab);
+  L.off_pmpart = take(sizeof(double) * L.need.partial);
+  L.off_hpack = take(L.need.pack);
+  L.off_sctab = take(sizeof(double) * L.need.table);
   L.off_nspart = take(sizeof(double) * L.ns_blocks);
-  int64_t maxI = 0;
-  for (int k = 0; k < N; ++k) maxI = std::max(maxI, p.dims[k]);
   L.off_M = take(sizeof(double) * (size_t)maxI * R);
   L.node_f64 = p.dtype == NNCP_F32 ? 1 : 0;
   for (int i = 0; i < L.ntn; ++i)
     if (L.tn[i].has_buf) L.tn[i].off = take((size_t)L.tn[i].rows * R * (L.node_f64 ? 8 : 4));
   L.off_dtA = L.off_dtB = 0;
   if (p.no_tree) {
-    // mode n from X directly: left with split n+1 (temporary over modes 1..n, then
-    // leading multi-TTVs down to mode n) or right with split n (temporary over
-    // modes n..N, then one trailing multi-TTV), whichever temporary is smaller
-    int64_t tmax = 1;
-    size_t part = 0, pack = 0;
-    for (int n = 0; n < N; ++n) {
-      const int64_t tl = n <= N - 2 ? prod_range(p, 0, n) : INT64_MAX;
-      const int64_t tr = n >= 1 ? prod_range(p, n, N - 1) : INT64_MAX;
-      const int side = tl <= tr ? 0 : 1;
-      const int s = side == 0 ? n + 1 : n;
-      L.dside[n] = side;
-      L.dsplit[n] = s;
-      const int64_t IL = prod_range(p, 0, s - 1), IR = p.I / IL;
-      L.dpm[n] = pm_plan(side, p.dtype, IL, IR, (int)(side == 0 ? p.dims[s] : p.dims[0]), R, p.wg_kib);
-      tmax = std::max(tmax, side == 0 ? tl : tr);
-      part = std::max(part, L.dpm[n].partial_doubles);
-      pack = std::max(pack, L.dpm[n].pack_bytes);
-      if (pm_sctab_doubles(L.dpm[n]) > tab) {
-        tab = pm_sctab_doubles(L.dpm[n]);
-        L.off_sctab = take(sizeof(double) * tab);  // relocated to fit the no-tree launches too
-      }
-    }
     const size_t tb = (size_t)tmax * R * (L.node_f64 ? 8 : 4);
     L.off_dtA = take(tb);
     L.off_dtB = take(tb);
-    for (int n = 0; n < N - 1; ++n)
-      if (L.dside[n] == 1) {
-        const int nz = mttv_trail_split(p.dims[n], prod_range(p, n + 1, N - 1), R);
-        if (nz > 1) part = std::max(part, (size_t)nz * (size_t)p.dims[n] * R);
-      }
-    if (part > part0 ||
-        pack > std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes)) {
-      // relocate the partial and pack regions to fit the no-tree launches too
-      L.off_pmpart = take(sizeof(double) * std::max(part, part0));
-      L.off_hpack = take(std::max(pack, std::max(L.pmL[0].pack_bytes, L.pmL[1].pack_bytes)));
-    }
   }
   L.total = o + 256;
   return L;
@@ -454,20 +470,19 @@ KrpDesc krp_for(const nncp_plan* P, int a, int b, bool scaled) {
 }
 
 // Partial MTTKRP of X split after mode s (0-based: rows are modes 0..s-1) on
-// `side`, with launch plan lp for the first column chunk, into T.
-hipError_t run_pm_at(const nncp_plan* P, int side, int s, const PmLaunch& lp, void* T, int t_f64, const void* X,
+// `side` into T, one launch per chunk of columns.
+hipError_t run_pm_at(const nncp_plan* P, int side, int s, const PmChunks& pc, void* T, int t_f64, const void* X,
                      bool scaled, const Sink& st) {
   const Problem& p = P->p;
-  const int I1 = (int)(side == 0 ? p.dims[s] : p.dims[0]);
-  const int64_t IL = prod_range(p, 0, s - 1), IR = p.I / IL;
-  for (int c0 = 0; c0 < p.R; c0 += kPmMaxCols) {
+  for (int c = 0; c < pc.n; ++c) {
+    if (!P->L.need.covers(pc.at[c])) return hipErrorInvalidValue;
     PmArgs a{};
     a.X = X;
-    a.IL = IL;
-    a.IR = IR;
+    a.IL = prod_range(p, 0, s - 1);
+    a.IR = p.I / a.IL;
     a.krp = side == 0 ? krp_for(P, s, p.N - 1, scaled) : krp_for(P, 0, s - 1, scaled);
-    a.R = std::min(kPmMaxCols, p.R - c0);
-    a.col0 = c0;
+    a.col0 = c * kPmMaxCols;
+    a.R = std::min(kPmMaxCols, p.R - a.col0);
     a.T = T;
     a.t_f64 = t_f64;
     a.partial = P->pmpart();
@@ -476,9 +491,8 @@ hipError_t run_pm_at(const nncp_plan* P, int side, int s, const PmLaunch& lp, vo
     a.sctab = P->sctab();
     a.zeros = P->zeros();
     a.counters = P->counters();
-    const PmLaunch l = (a.R == std::min(kPmMaxCols, p.R)) ? lp : pm_plan(side, p.dtype, IL, IR, I1, a.R, p.wg_kib);
-    pm_fill_args(l, a);
-    hipError_t e = pm_launch(l, a, st);
+    pm_fill_args(pc.at[c], a);
+    hipError_t e = pm_launch(pc.at[c], a, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -681,7 +695,37 @@ hipError_t enqueue_iteration(nncp_plan* P, const Sink& st0, std::vector<std::pai
   return mark(-1);
 }
 
+int plan_problem(Problem& p, int N, const int64_t* dims, int R, int dtype, int update, const nncp_options* opt) {
+  int st = fill_problem(p, N, dims, R, dtype, update, opt ? opt->split : 0);
+  if (st != NNCP_OK) return st;
+  p.wg_kib = opt ? opt->pm_wg_kib : 0;
+  p.no_tree = opt ? (opt->no_tree != 0) : 0;
+  p.sweeps = (opt && opt->inner_sweeps > 0) ? opt->inner_sweeps : 1;
+  if (p.sweeps > NNCP_MAX_SWEEPS) return NNCP_EINVAL;
+  p.inner_tol = opt ? opt->inner_tol : 0.0;
+  if (!(p.inner_tol >= 0.0) || !std::isfinite(p.inner_tol)) return NNCP_EINVAL;
+  p.peel = opt ? opt->tree_peel : 0;
+  return NNCP_OK;
+}
+
 }  // namespace
+
+namespace nncpk {
+int record_iteration(const void* X, int dtype, int N, const int64_t* dims, int R, int update, float* const* H,
+                     const nncp_options* opt, char* ws, size_t* ws_bytes, void* rec) {
+  nncp_plan P;
+  const int st = plan_problem(P.p, N, dims, R, dtype, update, opt);
+  if (st != NNCP_OK) return st;
+  P.L = make_layout(P.p);
+  P.X = X;
+  for (int k = 0; k < N; ++k) P.H[k] = H[k];
+  P.ws = ws;
+  *ws_bytes = P.L.total;
+  Sink sk;
+  sk.rec = rec;
+  return enqueue_iteration(&P, sk, nullptr) == hipSuccess ? NNCP_OK : NNCP_EDEVICE;
+}
+}  // namespace nncpk
 
 // ---------------------------------------------------------------------------
 // C ABI
@@ -725,15 +769,8 @@ int nncp_plan_create(nncp_plan** out, const void* X, int dtype, int N, const int
   if (!out || !X || !H) return NNCP_EINVAL;
   *out = nullptr;
   Problem p;
-  int st = fill_problem(p, N, dims, R, dtype, update, opt ? opt->split : 0);
+  int st = plan_problem(p, N, dims, R, dtype, update, opt);
   if (st != NNCP_OK) return st;
-  p.wg_kib = opt ? opt->pm_wg_kib : 0;
-  p.no_tree = opt ? (opt->no_tree != 0) : 0;
-  p.sweeps = (opt && opt->inner_sweeps > 0) ? opt->inner_sweeps : 1;
-  if (p.sweeps > NNCP_MAX_SWEEPS) return NNCP_EINVAL;
-  p.inner_tol = opt ? opt->inner_tol : 0.0;
-  if (!(p.inner_tol >= 0.0) || !std::isfinite(p.inner_tol)) return NNCP_EINVAL;
-  p.peel = opt ? opt->tree_peel : 0;
   for (int k = 0; k < N; ++k)
     if (!H[k]) return NNCP_EINVAL;
   nncp_plan* P = new (std::nothrow) nncp_plan();

@@ -332,6 +332,11 @@ inline int kslot(int kind) {
 }
 // Append a record (host), stamping its stage; returns hipSuccess.
 hipError_t sink_record(const Sink& s, const KOp& op);
+// The records (rec: std::vector<KOp>*) of one iteration of a plan whose workspace
+// lies at ws; its size is returned. Host only: no pointer is followed, so checks of
+// the plans' routes and address ranges need no device.
+int record_iteration(const void* X, int dtype, int N, const int64_t* dims, int R, int update, float* const* H,
+                     const nncp_options* opt, char* ws, size_t* ws_bytes, void* rec);
 
 // Persistent batched kernels: each has the signature
 //   (const BItem* items, const int* grp, const KOp* ops)
