@@ -8,6 +8,8 @@
 //    (Section IV-B, appendix algorithm), all accumulated in FP64 with a
 //    deterministic two-stage reduction;
 //  * ||X||^2 and FP32 -> BF16/FP16 quantisation of the stored tensor.
+#include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <vector>
 
@@ -907,11 +909,31 @@ __device__ __forceinline__ void gram1k_rows(const FinalizeArgs& a, int64_t r0, i
   }
   beta = 0.0;
   if (a.do_fit && a.M) {
-    const int64_t n = (r1 - r0) * R;
+    // element e = tid + NTF * q is row r0 + e mod cnt of column e / cnt; (k, rw) step
+    // with e, and four elements' loads are in flight
+    const int64_t cnt = r1 - r0, n = cnt * R;
+    const int64_t dk = NTF / cnt, drw = NTF - dk * cnt;
+    int64_t k = tid / cnt, rw = tid - k * cnt;
     double bsum = 0.0;
-    for (int64_t e = tid; e < n; e += NTF) {
-      const int64_t k = e / (r1 - r0), idx = r0 + (e - k * (r1 - r0)) + a.I * k;
-      bsum += (double)as_global(a.W)[idx] * ldv(a.M, idx, a.m_f64);
+    for (int64_t e = tid; e < n; e += 4 * NTF) {
+      float w[4];
+      double m[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool in = e + u * NTF < n;
+        const int64_t idx = in ? r0 + rw + a.I * k : r0;
+        w[u] = as_global(a.W)[idx];
+        m[u] = in ? ldv(a.M, idx, a.m_f64) : 0.0;
+        k += dk;
+        rw += drw;
+        if (rw >= cnt) {
+          rw -= cnt;
+          ++k;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (e + u * NTF < n) bsum += (double)w[u] * m[u];
     }
     beta = block_sum(bsum, sh);
   }
@@ -1500,14 +1522,21 @@ size_t fin_batch_max_lds() {
 // Row chunks for the Gram. R <= 64: a chunk's waves take about six groups of 16
 // rows each (fin_ns waves per column-block pair; twelve at R > 48, whose partials
 // are the largest to add up: 1344 x 50 in 14 chunks 8.6 + 14.4 us, in 7 12.5 + 8.4),
-// at most 32 chunks, one group without a second launch up to twice that; R > 64:
-// chunks of about 2^19 products, at most 64.
+// one group without a second launch up to twice that. Past 32 chunks the walk of a
+// chunk (about 1.5 us per two row groups of a wave) is set against the sum over the
+// chunks, and the least total lies near a multiple of sqrt(I), at most one chunk per
+// CU (us with 32 / 64 / 128 / 256 chunks: 100000 x 10 19 / 19 / 26 / 42, x 50 148 /
+// 103 / 102 / 147; 1000000 x 10 103 / 62 / 48 / 54, x 50 1459 / 763 / 436 / 314).
+// R > 64: chunks of about 2^19 products, at most 64.
 int finalize_chunks(int64_t I, int R, int* rows_per_chunk) {
   int64_t chunks;
   if (R <= kSmallMaxR) {
     const int64_t rows = 16 * (R > 48 ? 12 : 6) * fin_ns(R);
     chunks = I <= 2 * rows ? 1 : (I + rows - 1) / rows;
-    if (chunks > 32) chunks = 32;
+    if (chunks > 32) {
+      const int64_t c = (int64_t)((R <= 16 ? 0.15 : 0.28) * std::sqrt((double)I));
+      chunks = std::min(chunks, std::max<int64_t>(32, std::min<int64_t>(256, c)));
+    }
   } else {
     chunks = (I * R * R + (1ll << 19) - 1) >> 19;
     if (chunks > 64) chunks = 64;
