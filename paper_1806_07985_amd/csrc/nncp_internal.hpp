@@ -190,6 +190,7 @@ struct UpdateArgs {
                           // than tol x the row's largest entry
   double* W64;            // optional: the new W_hat also in FP64 (I x R, column-major)
 };
+int64_t update_lane_rows(int R, int update, int sweeps, double tol);
 hipError_t update_launch(const UpdateArgs& a, hipStream_t st);
 hipError_t update_launch(const UpdateArgs& a, const Sink& sk);
 

@@ -684,8 +684,7 @@ __global__ __launch_bounds__(NT) void update_reg_kernel(UpdateArgs a) {
   update_reg_body<RB>(a, blockIdx.x);
 }
 
-constexpr int kUpdLane = 100;         // update variants of one lane per row: 100 + registers
-constexpr int64_t kUpdLaneRows = 4096;
+constexpr int kUpdLane = 100;  // update variants of one lane per row: 100 + registers
 
 // Rows of W staged in LDS at a time (FP64): about 32 KB.
 __host__ __device__ inline int fin_sub_rows(int R) {
@@ -1421,18 +1420,33 @@ hipError_t mttv_lead_launch(const MttvArgs& a, const Sink& sk) {
   return record_or_launch(sk, K_MTTV_LEAD, gs * 10 + (a.t_f64 ? 1 : 0), blocks, 1, 0, k, &a, sizeof(a));
 }
 
+// Rows from which the update takes one lane per row (R <= 32; above, a row does not
+// fit a lane's registers). Below, a wave per row has the shorter chain. Lanes' time
+// hardly grows with the rows; per sweep it is R * rb products (rb register columns). A
+// wave's grows with them; per sweep it is a step per column (HALS, in eights), or the
+// products of W S at 0.6 of a step each (MU), and seven steps' worth of reductions if
+// the sweeps may stop early. With many sweeps the line is where those meet, with one
+// where loads and stores do. us, wave / lane per row: HALS R = 16, one sweep: 4096
+// rows 8 / 9, 32768 29 / 9; 50 sweeps: 4096 50 / 161, 16384 174 / 163, 32768 337 / 166; R = 5,
+// 50 sweeps: 8192 50 / 62, 12288 72 / 62, to a tolerance 8192 103 / 66; R = 32, one: 8192 18 / 19,
+// 50: 8192 176 / 567, 32768 652 / 573; MU R = 32, one: 12288 21 / 19, ten: 8192 28 / 118, 65536
+// 156 / 122.
+int64_t update_lane_rows(int R, int update, int sweeps, double tol) {
+  const int rb = R <= 16 ? 16 : 32;
+  const bool mu = update == NNCP_MU;
+  const double steps = (mu ? 0.6 * rb : (double)((R + 7) / 8 * 8)) + (tol > 0.0 ? 7.0 : 0.0);
+  const double one = std::max(256.0 * rb, mu ? 375.0 * R : 0.0);
+  const double many = std::max(one, 920.0 * R * rb / steps);
+  return (int64_t)(many - (many - one) * 2.0 / (std::max(sweeps, 1) + 1.0));
+}
+
 hipError_t update_launch(const UpdateArgs& a, const Sink& sk) {
   if (a.I <= 0) return hipSuccess;
   const int rpb = NT / 64;
   const unsigned g = (unsigned)((a.I + rpb - 1) / rpb);
   if (a.R <= 64) {
     const int rb = a.R <= 16 ? 16 : (a.R <= 32 ? 32 : 64);
-    // One lane per row from 4096 rows (R <= 16) or 8192 (R <= 32): below, the row's
-    // latency counts, and a wave per row has the shorter chain. us, wave / lane per
-    // row: R = 16, 4000 rows 6.4 / 6.9, 30012 rows 24 / 7.5; R = 32, 4000 rows 10.0 /
-    // 17.5, 8192 rows 18 / 17.5, 30012 rows 60 / 19. R > 32: a row does not fit a
-    // lane's registers.
-    if (a.R <= 32 && a.I >= (rb == 16 ? kUpdLaneRows : 2 * kUpdLaneRows)) {
+    if (a.R <= 32 && a.I >= update_lane_rows(a.R, a.update, a.sweeps, a.tol)) {
       const void* k = rb == 16 ? (const void*)update_lane_kernel<16> : (const void*)update_lane_kernel<32>;
       return record_or_launch(sk, K_UPDATE, kUpdLane + rb, (unsigned)((a.I + NT - 1) / NT), 1, 0, k, &a, sizeof(a));
     }
