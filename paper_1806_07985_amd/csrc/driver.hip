@@ -189,9 +189,8 @@ struct PmNeed {
 };
 
 struct Layout {
-  size_t off_zeros, off_alpha, off_iter, off_counters, off_lam, off_lammodel, off_lamin, off_G, off_S, off_fit,
+  size_t off_zeros, off_alpha, off_iter, off_lam, off_lammodel, off_lamin, off_G, off_S, off_fit,
       off_finpart, off_pmpart, off_hpack, off_sctab, off_nspart, off_M, total;
-  int ncounters;
   int node_f64;  // tree temporaries are FP64 for FP32 tensors, FP32 for 16-bit tensors
   // the tree: nodes, and per mode the nodes computed just before its update
   // (top-down; the last one is the leaf {n}, whose MTTKRP goes to M unless the
@@ -381,11 +380,9 @@ Layout make_layout(const Problem& p) {
     maxI = std::max(maxI, p.dims[k]);
   }
   L.ns_blocks = norm_sq_blocks(p.I);
-  L.ncounters = std::max(L.pmL[0].at[0].ncounters, L.pmL[1].at[0].ncounters) + 4;
   L.off_zeros = take(256);
   L.off_alpha = take(sizeof(double));
   L.off_iter = take(sizeof(int));
-  L.off_counters = take(sizeof(unsigned) * L.ncounters);
   L.off_lam = take(sizeof(double) * N * R);
   L.off_lammodel = take(sizeof(double) * R);
   L.off_lamin = take(sizeof(double) * R);
@@ -434,7 +431,6 @@ struct nncp_plan {
   unsigned* zeros() const { return at<unsigned>(L.off_zeros); }
   double* alpha() const { return at<double>(L.off_alpha); }
   int* iter() const { return at<int>(L.off_iter); }
-  unsigned* counters() const { return at<unsigned>(L.off_counters); }
   double* lam() const { return at<double>(L.off_lam); }
   double* lam_model() const { return at<double>(L.off_lammodel); }
   double* lam_in() const { return at<double>(L.off_lamin); }
@@ -490,7 +486,6 @@ hipError_t run_pm_at(const nncp_plan* P, int side, int s, const PmChunks& pc, vo
     a.hscale = P->hscale();
     a.sctab = P->sctab();
     a.zeros = P->zeros();
-    a.counters = P->counters();
     pm_fill_args(pc.at[c], a);
     hipError_t e = pm_launch(pc.at[c], a, st);
     if (e != hipSuccess) return e;
@@ -809,8 +804,7 @@ int nncp_plan_create(nncp_plan** out, const void* X, int dtype, int N, const int
     nncp_plan_destroy(P);
     return code;
   };
-  // zero counters, iteration counter, the zero block read by masked loads
-  if (fill_u32_launch(P->counters(), P->L.ncounters, 0u, s) != hipSuccess) return fail(NNCP_EDEVICE);
+  // the zero block read by masked loads, the iteration counter
   if (fill_u32_launch(P->zeros(), 64, 0u, s) != hipSuccess) return fail(NNCP_EDEVICE);
   if (fill_u32_launch((unsigned*)P->iter(), 1, 0u, s) != hipSuccess) return fail(NNCP_EDEVICE);
   // lambda_in
@@ -1126,9 +1120,7 @@ static int step_ctx(StepCtx& c, const void* X, int dtype, int N, const int64_t* 
   if (!c.mem.take(c.P.L.total, hs)) return NNCP_ENOMEM;
   c.P.ws = (char*)c.mem.p;
   if (hipDeviceSynchronize() != hipSuccess) return NNCP_EDEVICE;
-  // the zero block and the counters, with the two small fields between them
-  const int64_t words = (int64_t)(c.P.L.off_counters - c.P.L.off_zeros) / 4 + c.P.L.ncounters;
-  return fill_u32_launch(c.P.zeros(), words, 0u, hs) == hipSuccess ? NNCP_OK : NNCP_EDEVICE;
+  return fill_u32_launch(c.P.zeros(), 64, 0u, hs) == hipSuccess ? NNCP_OK : NNCP_EDEVICE;
 }
 
 int nncp_partial_mttkrp(const void* X, int dtype, int N, const int64_t* dims, int s, int side,

@@ -56,7 +56,6 @@ struct PmArgs {
   int t_f64;             // T is double (else float)
   double* partial;       // split-K partials (FP64)
   const void* zeros;     // >= 64 bytes of zeros in device memory (read by out-of-range lanes)
-  unsigned* counters;    // one per M tile; zero on entry, left zero on exit
   int nsplit;            // (n_i1blk / istages) * n_jblk
   int wm;                // waves along M in a work-group (1 or 4); the other 4 / wm split K
   int mtiles;            // M tiles of the output
@@ -100,7 +99,6 @@ struct PmLaunch {
   size_t lds_bytes;
   size_t partial_doubles;
   size_t pack_bytes;     // 16-bit tensors: bytes of the packed factor terms + scales
-  int ncounters;
 };
 
 // I1 = extent of the first contracted mode (mode s+1 for the left node, mode 1

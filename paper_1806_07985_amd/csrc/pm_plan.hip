@@ -219,7 +219,6 @@ static PmLaunch plan_impl(int side, int dtype, int64_t IL, int64_t IR, int I1, i
   L.pack_bytes =
       f32 ? 0 : (size_t)pm16_terms(dtype) * RP * L.I1pad * sizeof(unsigned short) + 256 + (size_t)RP * sizeof(float);
   L.partial_doubles = L.nsplit > 1 ? (size_t)L.nsplit * RP * (size_t)L.mtiles * L.mtile : 0;
-  L.ncounters = L.mtiles;
   return L;
 }
 

@@ -1513,16 +1513,7 @@ const void* small_batch_kernel_ptr(int kind, int variant) {
     default: return nullptr;
   }
 }
-const void* fin_batch_kernel_ptr() {
-  static bool attr = [] {
-    (void)hipFuncSetAttribute((const void*)fin_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)fin_batch_max_lds());
-    (void)hipGetLastError();
-    return true;
-  }();
-  (void)attr;
-  return (const void*)fin_batch_kernel;
-}
+const void* fin_batch_kernel_ptr() { return (const void*)fin_batch_kernel; }
 // The most dynamic LDS a 1024-thread Gram/finalize op of rank <= 64 uses.
 size_t fin_batch_max_lds() {
   size_t m = 0;
@@ -1567,16 +1558,6 @@ int finalize_chunks(int64_t I, int R, int* rows_per_chunk) {
 hipError_t finalize_launch(const FinalizeArgs& a, const Sink& sk) {
   const size_t RR = (size_t)a.R * a.R;
   if (a.R <= kSmallMaxR) {
-    static bool attr = [] {
-      const void* ks[] = {(const void*)fin1k_kernel<1>,        (const void*)fin1k_kernel<2>,
-                          (const void*)fin1k_kernel<4>,        (const void*)gram1k_chunk_kernel<1>,
-                          (const void*)gram1k_chunk_kernel<2>, (const void*)gram1k_chunk_kernel<4>};
-      for (const void* k : ks)
-        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024) != hipSuccess)
-          (void)hipGetLastError();
-      return true;
-    }();
-    (void)attr;
     const int ep = fin_ep(a.R);
     const size_t lds = (size_t)fin_work_doubles(a.R) * sizeof(double);
     if (a.nchunks <= 1) {
