@@ -68,10 +68,10 @@ struct PmArgs {
   // holds the inverse), laid out [term 0 rows RP][term 1 rows RP]... x I1pad
   unsigned short* hpack;
   float* hscale;
-  // Optional: the per-(j, column) Khatri-Rao scales of the whole launch in FP64,
+  // The per-(j, column) Khatri-Rao scales of the whole launch in FP64,
   // sctab[j * RP + r] (RP = 16 * nb), written by a pre-kernel before the partial
-  // MTTKRP (the launchers run it); the work-groups then copy their j block
-  // instead of each computing it. nullptr: every group computes its own block.
+  // MTTKRP (the launchers run it); the work-groups copy their j block. Required: a
+  // launch without it is refused.
   double* sctab;
 };
 

@@ -78,7 +78,7 @@ static int load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, i
 
 hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const int RP = 16 * L.nb;
-  if (!a.hpack || !a.hscale) return hipErrorInvalidValue;
+  if (!a.hpack || !a.hscale || !a.sctab) return hipErrorInvalidValue;
   const bool bf = L.dtype == NNCP_BF16;
   PackArgs pa{a.krp.f[0], a.I1, a.I1pad, a.R, a.col0, RP, a.hpack, a.hscale};
   const int wm = a.wm;
@@ -108,15 +108,12 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
     pm.gy = (unsigned)L.nsplit;
     pm.lds = (unsigned)lds;
     pm.u.pm = a;
-    if (a.sctab) {
-      e = pm_scale_table_record(L, a, sk);
-      if (e != hipSuccess) return e;
-    }
-    return sink_record(sk, pm);
+    e = pm_scale_table_record(L, a, sk);
+    return e == hipSuccess ? sink_record(sk, pm) : e;
   }
   {
     PmArgs sa = a;
-    int64_t n = a.sctab ? L.J * RP : 0;
+    int64_t n = L.J * RP;
     void* pargs[] = {(void*)&pa, (void*)&sa, (void*)&n};
     // one group per column: 1024 threads for a long one (I_1 = 30012: 52 us with 256)
     const int pt = a.I1pad > 2048 ? 1024 : 256;

@@ -62,8 +62,7 @@ __device__ __forceinline__ double krp_scale_entry(const KrpDesc& krp, uint32_t j
 }
 
 // The scale table of a launch: sctab[j * RP + r] = Krest(j, col0 + r) times
-// the column's 1/lambda product (0 for r >= R), j < J. The same function of
-// (j, column) the work-groups otherwise evaluate themselves.
+// the column's 1/lambda product (0 for r >= R), j < J.
 template <int NTH>
 __device__ __forceinline__ void scale_table_block(const PmArgs& a, int RP, int64_t n, int64_t blk) {
   const int64_t e = blk * NTH + threadIdx.x;

@@ -398,6 +398,7 @@ hipError_t pm_launch_f32(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const void* k = kernel_for(L.side, L.nb, ld, mt, L.xs, false);
   if (!k || (wm != 1 && wm != 4)) return hipErrorInvalidValue;
   if (L.xs && (wm != 4 || a.istages != 1)) return hipErrorInvalidValue;
+  if (!a.sctab) return hipErrorInvalidValue;
   size_t lds = L.lds_bytes;
   if (reduce_lds(L.side, L.nb, wm) > lds) lds = reduce_lds(L.side, L.nb, wm);
   if (lds > kPmMaxLds) return hipErrorInvalidValue;
@@ -409,16 +410,11 @@ hipError_t pm_launch_f32(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
     op.gy = (unsigned)L.nsplit;
     op.lds = (unsigned)lds;
     op.u.pm = a;
-    if (a.sctab) {
-      hipError_t e = pm_scale_table_record(L, a, sk);
-      if (e != hipSuccess) return e;
-    }
-    return sink_record(sk, op);
+    hipError_t e = pm_scale_table_record(L, a, sk);
+    return e == hipSuccess ? sink_record(sk, op) : e;
   }
-  if (a.sctab) {
-    hipError_t e = pm_scale_table_launch(L, a, sk.st);
-    if (e != hipSuccess) return e;
-  }
+  hipError_t e = pm_scale_table_launch(L, a, sk.st);
+  if (e != hipSuccess) return e;
   if (lds > 64 * 1024) pm_allow_lds(k, 160 * 1024);
   void* args[] = {(void*)&a};
   return hipLaunchKernel(k, dim3(L.mgroups, L.nsplit), dim3(NT), args, lds, sk.st);

@@ -178,8 +178,7 @@ static PmLaunch plan_impl(int side, int dtype, int64_t IL, int64_t IR, int I1, i
   int64_t jblk = cdiv(L.J, n_jblk < 1 ? 1 : n_jblk);
   if (jblk < min_j) jblk = min_j;
   // at most 64 j per group (a group's scales are a prologue of jblk * RP
-  // values: copied from the launch's table, or computed where there is none),
-  // or 128 for an FP32 launch that still has two rounds of groups or more with
+  // values, copied from the launch's table), or 128 for an FP32 launch that still has two rounds of groups or more with
   // it (the 64^5 left node: 4096 -> 2048 groups, 0.85 -> 0.76 ms; fewer groups
   // than that would leave CUs unevenly loaded), unless that leaves a few groups
   // beyond the target -- a second, mostly idle round for a 16-bit kernel (one
