@@ -319,6 +319,16 @@ int nncp_norm_sq(const void* X, int dtype, int64_t n, double* out_dev, void* str
 int nncp_norm_sq_noalloc(const void* X, int dtype, int64_t n, double* out_dev, void* stream);
 
 /*
+ * Scratch of the step calls (nncp_norm_sq, nncp_partial_mttkrp, nncp_mttkrp,
+ * nncp_gram, nncp_nls_solve): kept between calls, at most two blocks of 64 MiB per
+ * GPU, until the process ends, an allocation of this library fails on that GPU, or
+ * this call, which frees what the current device holds. It is part of no workspace
+ * size and of no server's HBM budget. Safe beside running calls, whose own scratch is
+ * not on the shelf. Always NNCP_OK.
+ */
+int nncp_release_scratch(void);
+
+/*
  * Partial MTTKRP for a root branch of the dimension tree (Section IV-A, Fig. 2a):
  * with I_L = I_1*...*I_s and I_R = I_{s+1}*...*I_N, view X as the column-major
  * I_L x I_R matrix X_[L].

@@ -48,7 +48,8 @@ namespace {
 // hipFree's wait for the whole device, took longer than the kernels of a small call
 // (37x29x31x23x19 MTTKRP, R = 16: 98 -> 62 us a call; 400x300x200 partial MTTKRP, R = 96:
 // 158 -> 109; NLS of 1344 rows, R = 50: 150 -> 147). Kept blocks are given back
-// where an allocation of a plan or a call fails.
+// where an allocation of the library fails (plans, calls, batches, served jobs) and
+// by nncp_release_scratch.
 struct Shelf {
   struct Block {
     void* p;
@@ -749,6 +750,11 @@ const char* nncp_strerror(int s) {
 
 int nncp_version(void) { return 100; }
 
+int nncp_release_scratch(void) {
+  (void)release_scratch();
+  return NNCP_OK;
+}
+
 size_t nncp_workspace_bytes(int N, const int64_t* dims, int R, int dtype, const nncp_options* opt) {
   Problem p;
   if (fill_problem(p, N, dims, R, dtype, NNCP_HALS, opt ? opt->split : 0) != NNCP_OK) return 0;
@@ -1346,7 +1352,7 @@ int ensure_dev(T** p, size_t* cap, size_t n, size_t floor, bool* moved) {
   // headroom, so that members joining later rarely need a larger list: at
   // least `floor` entries, else half again the current need
   size_t want = n < floor ? floor : n + n / 2;
-  if (hipMalloc((void**)p, want * sizeof(T)) != hipSuccess) return NNCP_ENOMEM;
+  if (device_malloc((void**)p, want * sizeof(T)) != hipSuccess) return NNCP_ENOMEM;
   *cap = want;
   return NNCP_OK;
 }
@@ -1532,6 +1538,8 @@ namespace nncpk {
 namespace {
 std::atomic<uint64_t> g_last_device_error{0};
 }
+
+bool release_scratch() { return g_shelf.release(current_device()); }
 
 void note_device_error(int hip_error, int where) {
   g_last_device_error.store(((uint64_t)(uint32_t)hip_error << 32) | (uint32_t)where, std::memory_order_relaxed);

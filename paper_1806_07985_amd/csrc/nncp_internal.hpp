@@ -337,6 +337,10 @@ hipError_t sink_record(const Sink& s, const KOp& op);
 int record_iteration(const void* X, int dtype, int N, const int64_t* dims, int R, int update, float* const* H,
                      const nncp_options* opt, char* ws, size_t* ws_bytes, void* rec);
 
+// Frees the scratch that the step calls keep on the current device; true if there
+// was any (an allocation that failed may then be tried again).
+bool release_scratch();
+
 // Persistent batched kernels: each has the signature
 //   (const BItem* items, const int* grp, const KOp* ops)
 // and its work-group b walks items grp[0] + b, grp[0] + b + gridDim.x, ...

@@ -121,25 +121,32 @@ void release_device(nncp_server* S, Job* j) {
   for (auto& h : j->Hd) h = nullptr;
 }
 
+// Stream-ordered allocation; one that fails is tried again without the scratch that
+// the library's step calls keep.
+hipError_t malloc_async(void** p, size_t bytes, hipStream_t s) {
+  hipError_t e = hipMallocAsync(p, bytes, s);
+  if (e != hipSuccess && nncpk::release_scratch()) e = hipMallocAsync(p, bytes, s);
+  return e;
+}
+
 // Loader thread: allocate, upload the tensor and starting factors, and build
 // the job's plan, all on the loader's stream.
 int load_device(nncp_server* S, Job* j) {
   hipStream_t s = S->up;
   const size_t xb = (size_t)j->I * elem_bytes(j->dtype);
-  if (hipMallocAsync(&j->Xd, xb, s) != hipSuccess) return NNCP_ENOMEM;
+  if (malloc_async(&j->Xd, xb, s) != hipSuccess) return NNCP_ENOMEM;
   if (hip_failed(hipMemcpyAsync(j->Xd, j->X, xb, hipMemcpyHostToDevice, s), __LINE__)) return NNCP_EDEVICE;
   for (int n = 0; n < j->N; ++n) {
     const size_t hb = (size_t)j->dims[n] * j->R * sizeof(float);
-    if (hipMallocAsync((void**)&j->Hd[n], hb, s) != hipSuccess) return NNCP_ENOMEM;
+    if (malloc_async((void**)&j->Hd[n], hb, s) != hipSuccess) return NNCP_ENOMEM;
     if (hip_failed(hipMemcpyAsync(j->Hd[n], j->H0[n].data(), hb, hipMemcpyHostToDevice, s), __LINE__))
       return NNCP_EDEVICE;
   }
   nncp_options o{};
   o.split = j->split;
-  o.no_graph = 1;  // advanced by the batch's graph only
   const size_t wsb = nncp_workspace_bytes(j->N, j->dims, j->R, j->dtype, &o);
   if (wsb == 0) return NNCP_EINVAL;
-  if (hipMallocAsync(&j->ws, wsb, s) != hipSuccess) return NNCP_ENOMEM;
+  if (malloc_async(&j->ws, wsb, s) != hipSuccess) return NNCP_ENOMEM;
   // plan set-up runs on the loader's stream and synchronises it; the plan's
   // later calls (finish, fits) are the worker's
   int r = nncp_plan_create(&j->plan, j->Xd, j->dtype, j->N, j->dims, j->R, j->update, j->Hd, nullptr, j->ws, wsb,

@@ -125,6 +125,8 @@ def _declare(L):
     L.nncp_quantize.argtypes = [c_vp, c_vp, ctypes.c_int, ctypes.c_int64, c_vp]
     L.nncp_norm_sq.restype = ctypes.c_int
     L.nncp_norm_sq.argtypes = [c_vp, ctypes.c_int, ctypes.c_int64, c_vp, c_vp]
+    L.nncp_release_scratch.restype = ctypes.c_int
+    L.nncp_release_scratch.argtypes = []
     L.nncp_norm_sq_noalloc.restype = ctypes.c_int
     L.nncp_norm_sq_noalloc.argtypes = [c_vp, ctypes.c_int, ctypes.c_int64, c_vp, c_vp]
     L.nncp_partial_mttkrp.restype = ctypes.c_int
@@ -583,6 +585,11 @@ def norm_sq(X, stream=None) -> float:
     out = torch.zeros(1, dtype=torch.float64, device=X.device)
     _check(lib().nncp_norm_sq(_ptr(X), _dtype_code(X), X.numel(), _ptr(out), _stream(stream)), "nncp_norm_sq")
     return float(out.item())
+
+
+def release_scratch():
+    """Give back the scratch that the step calls keep on the current device."""
+    _check(lib().nncp_release_scratch(), "nncp_release_scratch")
 
 
 def norm_sq_noalloc(X, out, stream=None):
