@@ -139,6 +139,9 @@ bool pm_f32_fast(int side, int64_t IL, int I1, int nb, bool xs = false);
 bool pm_f32_buf(int side, int64_t IL, int nb);
 bool pm16_fast(int side, int64_t IL, int I1, int nb);
 bool pm16_buf(int side, int64_t IL, int nb, int j1);
+// The load form a launch takes (pm_f32_body.hpp, pm16_body.hpp: LD_*).
+int pm_f32_load_form(const PmLaunch& L, int64_t IL, int I1);
+int pm16_load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1);
 template <int DT>
 const void* pm16_pack_kernel(bool batch, int threads);
 // Batched (work-list) forms of the partial-MTTKRP kernels, by recorded variant.

@@ -201,9 +201,10 @@ __device__ __forceinline__ void reduce_waves(float (&accf)[NACC][4], double* lds
 // earlier and the dword after them (the other lanes: none), and the step shifts
 // them into place: 31 us (35 if every lane loads the dword after). Every dword read
 // holds an element of the tensor, whose start is a dword's start.
-// LD_GEN: the rest (columns of hundreds of MB): a uniform check per step, masked
-// element loads in the steps that reach the tensor's end; their branches make the
-// compiler wait for every load in flight once per ring round.
+// LD_GEN: the rest (ragged, columns of 33 MB and more on the right, or 69 MB on the
+// left): a uniform check per step, masked element loads in the steps that reach the
+// tensor's end; their branches make the compiler wait for every load in flight once
+// per ring round.
 enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2, LD_BUFH = 3 };
 template <int L, bool NTL>
 __device__ __forceinline__ u16v<L> buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {

@@ -69,7 +69,7 @@ static bool from_dwords(const PmLaunch& L, const void* X, int64_t IR, int I1) {
   if (L.wm == 4 && IR <= pm_16_wave_rows(1, L.nb, L.j1)) return false;
   return L.nb < 4 || I1 > 16;
 }
-static int load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
+int pm16_load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
   const bool fast = pm16_fast(L.side, IL, I1, L.nb);
   if (fast && (L.side == 1 || IL % 64 == 0)) return 1;
   if (pm16_buf(L.side, IL, L.nb, L.j1)) return from_dwords(L, X, IR, I1) ? 3 : 2;
@@ -82,7 +82,7 @@ hipError_t pm_launch_16(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const bool bf = L.dtype == NNCP_BF16;
   PackArgs pa{a.krp.f[0], a.I1, a.I1pad, a.R, a.col0, RP, a.hpack, a.hscale};
   const int wm = a.wm;
-  const int ld = load_form(L, a.X, a.IL, a.IR, a.I1);
+  const int ld = pm16_load_form(L, a.X, a.IL, a.IR, a.I1);
   const bool mt = L.mper > 1;
   // variant = j1*100000 + bf16*10000 + side*1000 + nb*100 + mt*10 + load form
   const int variant =

@@ -40,7 +40,8 @@ namespace pm32 {
 // plain vector loads, where the shape guarantees that all of them lie inside the
 // tensor (pm_f32_fast). LD_GEN: a uniform check per step and masked loads in the
 // steps that reach the tensor's end; its branches make the compiler wait for all
-// loads in flight once per ring round; it serves columns of hundreds of MB.
+// loads in flight once per ring round; it serves ragged tensors whose matricisation
+// has columns of 34 MB and more on the right (67 at R > 32) or 143 MB on the left.
 // The streaming (nontemporal) hint goes with LD_FAST and LD_BUFNT on the left,
 // where a tensor's columns start on cache lines: every line is then read once, by
 // one load (128^4 left node 0.18 ms with the hint, 0.20 without; 1024^3 0.69 and

@@ -41,3 +41,24 @@ def _check(dims, s, side, R, dt, density, offset=10003):
 @pytest.mark.parametrize("R", [5, 20])
 def test_first_factor_past_31_bit_offsets(gpu_lib, R):
     _check((9000001 if R > 16 else 17000001, 3), 1, 1, R, "f32", 0.02)
+
+
+# masked loads: ragged, lane offsets past 31 bits (one j and several, each column-block count)
+@pytest.mark.parametrize("dims,s,side,R,dt", [
+    ((9000001, 3), 1, 1, 5, "f32"), ((3001, 3001, 3), 2, 1, 20, "f32"), ((4201, 4201, 3), 2, 1, 40, "f32"),
+    ((6001, 6001, 3, 2), 2, 0, 5, "f32"), ((6001, 6001, 3), 2, 0, 20, "f32"), ((6001, 6001, 2), 2, 0, 33, "f32"),
+    ((4201, 4201, 3), 2, 1, 5, "bf16"), ((4201, 4201, 3), 2, 1, 20, "f16"), ((4201, 4201, 2), 2, 1, 40, "bf16"),
+    ((17000001, 2), 1, 1, 5, "f16"), ((6001, 6001, 3, 2), 2, 0, 5, "f16"), ((6001, 6001, 3), 2, 0, 20, "bf16"),
+    ((6001, 6001, 2), 2, 0, 33, "f16")])
+def test_columns_past_31_bit_offsets(gpu_lib, dims, s, side, R, dt):
+    _check(dims, s, side, R, dt, 0.02)
+
+
+# 16-bit right nodes with one j, K split over i1 blocks, several tiles per group; the last
+# i1 block, tile group and tile ragged, on a dword and not
+@pytest.mark.parametrize("dims", [(6501, 33000), (6500, 33001), (3201, 70001)])
+@pytest.mark.parametrize("R", [10, 20])
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("offset", [10002, 10003])
+def test_j1_nodes_that_split_k_over_several_tiles(gpu_lib, dims, R, dt, offset):
+    _check(dims, 1, 1, R, dt, 0.5, offset)
