@@ -232,14 +232,14 @@ def _batch_study(dev, n_jobs, iters, wg_kib=0):
     gen_s = time.perf_counter() - t0
     entries = sum(int(np.prod(j["dims"])) for j in jobs)
 
-    def plans(graph):
+    def plans():
         out = []
         for j in jobs:
             H = [native.factor_to_device(h, device=dev) for h in j["H0"]]
-            out.append((native.Plan(j["X"], list(j["dims"]), j["R"], H, graph=graph, pm_wg_kib=wg_kib), H))
+            out.append((native.Plan(j["X"], list(j["dims"]), j["R"], H, pm_wg_kib=wg_kib), H))
         return out
 
-    mixed = plans(graph=False)
+    mixed = plans()
     batch = native.Batch()
     for p_, _ in mixed:
         batch.add(p_)
@@ -250,7 +250,7 @@ def _batch_study(dev, n_jobs, iters, wg_kib=0):
     torch.cuda.synchronize()
     t_batch = time.perf_counter() - t0
     st = batch.stats()
-    alone = plans(graph=True)
+    alone = plans()
     for p_, _ in alone:                  # untimed, as the batch's first tick: one iteration
         p_.run(1)
     torch.cuda.synchronize()
@@ -523,7 +523,7 @@ def main(argv=None):
 
     # phase breakdown (events between kernels)
     Hp = [native.factor_to_device(h, device=dev) for h in H0]
-    pplan = native.Plan(Xd, dims, R, Hp, update=args.update, split=s, graph=False, phase_timers=True)
+    pplan = native.Plan(Xd, dims, R, Hp, update=args.update, split=s, phase_timers=True)
     pplan.run(3)
     ph = pplan.phase_ms()
     pplan.close()

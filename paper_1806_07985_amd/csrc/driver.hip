@@ -638,7 +638,7 @@ FinalizeArgs fin_args(const nncp_plan* P, int n, const void* M, int m_f64, int s
 
 enum { PH_PM = 0, PH_MTTV = 1, PH_NLS = 2, PH_GRAM = 3, PH_ERR = 4, PH_TOTAL = 5 };
 
-// Enqueue one outer iteration. With timers, events bracket each phase (no graph).
+// Enqueue one outer iteration. With timers, events bracket each phase.
 hipError_t enqueue_iteration(nncp_plan* P, const Sink& st0, std::vector<std::pair<int, hipEvent_t>>* marks) {
   const Problem& p = P->p;
   auto mark = [&](int phase) -> hipError_t {

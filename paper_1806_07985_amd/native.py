@@ -286,6 +286,7 @@ def nncp(X, dims, R, iters, H, lam=None, update="hals", split=0, graph=True, rec
          peel=0):
     """Run the full driver. H: list of device (R, I_n) float32 tensors, updated in place.
 
+    graph is accepted and selects nothing (kernels are launched one by one).
     Returns dict(fit=np.ndarray, lam=np.ndarray, iters_done=int).
     """
     import torch
@@ -352,7 +353,8 @@ def autotune_tree(X, dims, R, H, reps=3, cap=64, pm_wg_kib=0, stream=None):
 
 
 class Plan:
-    """Persistent driver state: create once, run repeatedly, finish to normalise."""
+    """Persistent driver state: create once, run repeatedly, finish to normalise.
+    graph is accepted and selects nothing (kernels are launched one by one)."""
 
     def __init__(self, X, dims, R, H, lam=None, update="hals", split=0, graph=True, phase_timers=False,
                  workspace=None, stream=None, pm_wg_kib=0, no_tree=False, inner_sweeps=1, inner_tol=0.0, peel=0):
