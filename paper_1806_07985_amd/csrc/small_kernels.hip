@@ -910,9 +910,9 @@ __device__ __forceinline__ void gram1k_rows(const FinalizeArgs& a, int64_t r0, i
   if (a.do_fit && a.M) {
     // element e = tid + NTF * q is row r0 + e mod cnt of column e / cnt; (k, rw) step
     // with e, and four elements' loads are in flight
-    const int64_t cnt = r1 - r0, n = cnt * R;
-    const int64_t dk = NTF / cnt, drw = NTF - dk * cnt;
-    int64_t k = tid / cnt, rw = tid - k * cnt;
+    const unsigned cnt = (unsigned)(r1 - r0), dk = NTF / cnt, drw = NTF - dk * cnt;  // (an extent is below 2^31)
+    const int64_t n = (int64_t)cnt * R;
+    unsigned k = tid / cnt, rw = tid - k * cnt;
     double bsum = 0.0;
     for (int64_t e = tid; e < n; e += 4 * NTF) {
       float w[4];
@@ -920,7 +920,7 @@ __device__ __forceinline__ void gram1k_rows(const FinalizeArgs& a, int64_t r0, i
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const bool in = e + u * NTF < n;
-        const int64_t idx = in ? r0 + rw + a.I * k : r0;
+        const int64_t idx = in ? r0 + rw + a.I * (int64_t)k : r0;
         w[u] = as_global(a.W)[idx];
         m[u] = in ? ldv(a.M, idx, a.m_f64) : 0.0;
         k += dk;
