@@ -62,3 +62,11 @@ def test_columns_past_31_bit_offsets(gpu_lib, dims, s, side, R, dt):
 @pytest.mark.parametrize("offset", [10002, 10003])
 def test_j1_nodes_that_split_k_over_several_tiles(gpu_lib, dims, R, dt, offset):
     _check(dims, 1, 1, R, dt, 0.5, offset)
+
+
+@pytest.mark.parametrize("t", [1, 3, 4, 5, 15, 16, 17, 19, 20, 21, 31, 32, 37])
+@pytest.mark.parametrize("R", [3, 40])
+def test_split_sums_of_every_length(gpu_lib, t, R):
+    """About t splits over K: the sum's runs of sixteen, of four and its rest."""
+    _check((16, 64 * t, 7), 2, 1, R, "f32", 0.5)
+    _check((16, 64 * t, 7), 2, 1, R, "bf16", 0.5)
