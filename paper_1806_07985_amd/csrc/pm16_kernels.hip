@@ -60,19 +60,26 @@ size_t pm_16_reduce_lds(int side, int nb, int wm) {
 // the masked loads with the hint (1338 range-checked with it).
 // A right node of odd I_1 loads from dword starts (LD_BUFH) where the address unit is
 // what its waves wait for: F16 83x71x57x45 R = 24 59 -> 31 us, BF16 301x40000 R = 10 30
-// -> 19, 83x71x2565 R = 48 63 -> 45. Not where one wave is alone on its CU and waits
-// for its own loads (83x64x9, R = 5: 64 -> 89 us), and not with four column blocks
-// where most of a k-step is padding (15x20x40001 R = 40 80 -> 84, 31x5x40001 R = 48
-// 66 -> 61).
-static bool from_dwords(const PmLaunch& L, const void* X, int64_t IR, int I1) {
+// -> 19, 83x71x2565 R = 48 63 -> 45. Elsewhere the dword after each run is one more load
+// to wait for, and the plain range-checked loads are the faster ones:
+//  * columns below about 20 elements, 64 of which lie in a few cache lines (3x2x100000
+//    R = 5 233 -> 199 us, 1x6x7000 R = 20 193 -> 166);
+//  * few columns, as most lanes of a load are idle: up to 16 (R <= 16), 20 and 28 (R > 32;
+//    363x3000x5 74 -> 52 us, R = 50 134 -> 108; equal at 17 to 40 columns, by rank);
+//  * a small tensor's one group of four waves with columns for one of them or little
+//    more (17x50x70 R = 20 54 -> 46 us; equal at about 100 columns, 190 at R > 32);
+//  * four column blocks where most of a k-step is padding (15x20x40001 R = 40 84 -> 80;
+//    but 31x5x40001 R = 48 66 -> 61 from dword starts).
+static bool from_dwords(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
   if (L.side != 1 || !(I1 & 1) || ((uintptr_t)X & 3) != 0) return false;
-  if (L.wm == 4 && IR <= pm_16_wave_rows(1, L.nb, L.j1)) return false;
+  if (IL <= 20 || IR <= 12 + 4 * L.nb) return false;
+  if (L.wm == 4 && IR < (L.nb < 4 ? 96 : 192)) return false;
   return L.nb < 4 || I1 > 16;
 }
 int pm16_load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
   const bool fast = pm16_fast(L.side, IL, I1, L.nb);
   if (fast && (L.side == 1 || IL % 64 == 0)) return 1;
-  if (pm16_buf(L.side, IL, L.nb, L.j1)) return from_dwords(L, X, IR, I1) ? 3 : 2;
+  if (pm16_buf(L.side, IL, L.nb, L.j1)) return from_dwords(L, X, IL, IR, I1) ? 3 : 2;
   return fast ? 1 : 0;
 }
 

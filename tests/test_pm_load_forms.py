@@ -32,9 +32,9 @@ def walk(tmp_path_factory):
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
 
-    def run(shapes, ranks):
-        lines = [f"{dt} {math.prod(d[:s])} {math.prod(d[s:])} {d[s]} {d[0]} {R} {off}" for d in shapes for s in range(1, len(d))
-                 for R in ranks for dt in range(3) for off in ((0, 1) if dt else (0,))]
+    def run(shapes, ranks, lines=None):
+        lines = lines or [f"{dt} {math.prod(d[:s])} {math.prod(d[s:])} {d[s]} {d[0]} {R} {off}" for d in shapes
+                          for s in range(1, len(d)) for R in ranks for dt in range(3) for off in ((0, 1) if dt else (0,))]
         r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=900)
         assert r.returncode == 0 and f"{len(lines)} cases" in r.stdout, r.stdout[-3000:]
         return {ln[6:] for ln in r.stdout.splitlines() if ln.startswith("cover")}
@@ -60,3 +60,16 @@ def test_loads_of_long_columns(walk):
     seen = walk(LONG, (5, 20, 40))
     for what in ("f32 side 0", "f32 side 1", "16 side 0", "16 side 1"):
         assert any(s.startswith(what + " form 0") for s in seen), what
+
+
+@pytest.mark.parametrize("d,R,form", [((83, 71, 2565), 24, 3), ((301, 1, 40000), 10, 3), ((31, 5, 40001), 48, 3),  # the address unit is busy
+                                      ((3, 2, 100000), 5, 2), ((1, 6, 7000), 20, 2),            # short columns
+                                      ((363, 400, 5), 5, 2), ((363, 400, 20), 20, 2), ((363, 400, 28), 50, 2),  # few columns
+                                      ((363, 400, 17), 5, 3), ((363, 400, 21), 20, 3), ((363, 400, 29), 50, 3),
+                                      ((17, 50, 70), 20, 2), ((17, 50, 96), 20, 3), ((31, 50, 191), 50, 2),      # one group
+                                      ((15, 20, 4001), 40, 2)])                                   # padding
+def test_right_nodes_load_from_dword_starts_where_that_is_faster(walk, d, R, form):
+    """16-bit right node (split 2) of odd first extent; a tensor off a dword never does."""
+    for off, f in ((0, form), (1, 2)):
+        seen = walk(None, None, [f"2 {d[0] * d[1]} {d[2]} {d[2]} {d[0]} {R} {off}"])
+        assert any(s.startswith(f"16 side 1 form {f}") for s in seen), (off, sorted(seen))
