@@ -66,7 +66,7 @@ def test_loads_of_long_columns(walk):
                                       ((3, 2, 100000), 5, 2), ((1, 6, 7000), 20, 2),            # short columns
                                       ((363, 400, 5), 5, 2), ((363, 400, 20), 20, 2), ((363, 400, 28), 50, 2),  # few columns
                                       ((363, 400, 17), 5, 3), ((363, 400, 21), 20, 3), ((363, 400, 29), 50, 3),
-                                      ((17, 50, 70), 20, 2), ((17, 50, 96), 20, 3), ((31, 50, 191), 50, 2),      # one group
+                                      ((17, 50, 70), 20, 2), ((17, 50, 96), 20, 3), ((31, 10, 191), 50, 2),      # one group
                                       ((15, 20, 4001), 40, 2)])                                   # padding
 def test_right_nodes_load_from_dword_starts_where_that_is_faster(walk, d, R, form):
     """16-bit right node (split 2) of odd first extent; a tensor off a dword never does."""
