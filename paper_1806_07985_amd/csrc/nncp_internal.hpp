@@ -139,8 +139,18 @@ bool pm_f32_fast(int side, int64_t IL, int I1, int nb, bool xs = false);
 bool pm_f32_buf(int side, int64_t IL, int nb);
 bool pm16_fast(int side, int64_t IL, int I1, int nb);
 bool pm16_buf(int side, int64_t IL, int nb, int j1);
+// Left nodes whose tensor is streamed with the nontemporal hint though its columns do
+// not start on cache lines: a line that two waves share is fetched twice then, but
+// from about 12 GB on, with columns of 1 KB and more, that costs less than what
+// keeping the lines does (ms without / with the hint: FP32 30013x1200x50 R = 32 1.63 / 1.81,
+// x85 2.96 / 2.90, x200 7.02 / 6.62; 2001x2001x300 1.12 / 1.15, x1500 5.99 / 5.58; BF16
+// 30012x1200x48 R = 10 0.70 / 0.77, x150 2.47 / 2.45, x500 8.67 / 8.00; but columns of 604
+// bytes, 302x302x88000, 3.93 / 4.23).
+constexpr bool pm_left_stream(int64_t IL, int64_t IR, int64_t elem) {
+  return IL * elem >= 1024 && IL * IR >= 12000000000 / elem;
+}
 // The load form a launch takes (pm_f32_body.hpp, pm16_body.hpp: LD_*).
-int pm_f32_load_form(const PmLaunch& L, int64_t IL, int I1);
+int pm_f32_load_form(const PmLaunch& L, int64_t IL, int64_t IR, int I1);
 int pm16_load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1);
 template <int DT>
 const void* pm16_pack_kernel(bool batch, int threads);

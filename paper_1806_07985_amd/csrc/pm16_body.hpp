@@ -205,7 +205,8 @@ __device__ __forceinline__ void reduce_waves(float (&accf)[NACC][4], double* lds
 // left): a uniform check per step, masked element loads in the steps that reach the
 // tensor's end; their branches make the compiler wait for every load in flight once
 // per ring round.
-enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2, LD_BUFH = 3 };
+// LD_BUFNT: LD_BUF with the streaming hint (stand-alone left nodes).
+enum : int { LD_GEN = 0, LD_FAST = 1, LD_BUF = 2, LD_BUFH = 3, LD_BUFNT = 4 };
 template <int L, bool NTL>
 __device__ __forceinline__ u16v<L> buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   constexpr int aux = NTL ? kBufNt : 0;
@@ -768,7 +769,7 @@ __device__ __forceinline__ void right_body(const PmArgs& a, int bx, int by) {
 }
 
 // NTL: tensor loads with the streaming hint: stand-alone left nodes whose columns
-// start on cache lines (see pm_f32_body.hpp).
+// start on cache lines, and those of the largest tensors (see pm_f32_body.hpp).
 template <int DT, int SIDE, int NB, bool J1, int LD, bool MT, bool NTL>
 __device__ __forceinline__ void body(const PmArgs& a, int bx, int by) {
   if (SIDE == 0) left_body<DT, NB, LD, MT, NTL>(a, bx, by);
@@ -779,6 +780,10 @@ __device__ __forceinline__ void body(const PmArgs& a, int bx, int by) {
 template <int DT, int SIDE, int NB, bool J1, int LD, bool MT>
 __global__ __launch_bounds__(NT, 1) void pm16_kernel_std(PmArgs a) {
   body<DT, SIDE, NB, J1, LD, MT, SIDE == 0 && LD == LD_FAST>(a, blockIdx.x, blockIdx.y);
+}
+template <int DT, int NB, bool MT>
+__global__ __launch_bounds__(NT, 1) void pm16_left_nt(PmArgs a) {
+  body<DT, 0, NB, false, LD_BUF, MT, true>(a, blockIdx.x, blockIdx.y);
 }
 // Persistent batched form: items grp[0] + b, grp[0] + b + gridDim.x, ... below
 // grp[0] + grp[1], each one (M tile, split) work-group of a recorded launch.
@@ -841,11 +846,22 @@ const void* pick_side(int side, int nb, int j1, bool batch) {
 }
 
 template <int DT, bool MT>
+const void* pick_left_nt(int nb) {
+  switch (nb) {
+    case 1: return (const void*)pm16_left_nt<DT, 1, MT>;
+    case 2: return (const void*)pm16_left_nt<DT, 2, MT>;
+    case 4: return (const void*)pm16_left_nt<DT, 4, MT>;
+    default: return nullptr;
+  }
+}
+
+template <int DT, bool MT>
 const void* pick_load(int side, int nb, int j1, int ld, bool batch) {
   switch (ld) {
     case LD_FAST: return pick_side<DT, LD_FAST, MT>(side, nb, j1, batch);
     case LD_BUF: return pick_side<DT, LD_BUF, MT>(side, nb, j1, batch);
     case LD_BUFH: return pick_side<DT, LD_BUFH, MT>(side, nb, j1, batch);
+    case LD_BUFNT: return side == 0 && !batch ? pick_left_nt<DT, MT>(nb) : pick_side<DT, LD_BUF, MT>(side, nb, j1, batch);
     default: return pick_side<DT, LD_GEN, MT>(side, nb, j1, batch);
   }
 }

@@ -52,9 +52,10 @@ size_t pm_16_reduce_lds(int side, int nb, int wm) {
 }
 
 // Which loads a launch uses (pm16_body.hpp: 0 masked, 1 plain, 2 range-checked, 3
-// range-checked from dword starts):
+// range-checked from dword starts, 4 range-checked with the streaming hint):
 // plain ones for a right node, or a left node whose columns start on cache lines,
-// if the shape allows them; range-checked without the streaming hint for the rest.
+// if the shape allows them; range-checked for the rest, without the hint but for the
+// largest tensors (pm_left_stream).
 // F16 83x71x57x45 R = 24 left node 34.9 -> 28.7 us, BF16 200x180x220 R = 32 right
 // node 39.9 -> 27.0, BF16 30012x1200x48 R = 10 right node 1361 -> 843 us against
 // the masked loads with the hint (1338 range-checked with it).
@@ -79,7 +80,10 @@ static bool from_dwords(const PmLaunch& L, const void* X, int64_t IL, int64_t IR
 int pm16_load_form(const PmLaunch& L, const void* X, int64_t IL, int64_t IR, int I1) {
   const bool fast = pm16_fast(L.side, IL, I1, L.nb);
   if (fast && (L.side == 1 || IL % 64 == 0)) return 1;
-  if (pm16_buf(L.side, IL, L.nb, L.j1)) return from_dwords(L, X, IL, IR, I1) ? 3 : 2;
+  if (pm16_buf(L.side, IL, L.nb, L.j1)) {
+    if (L.side == 0) return pm_left_stream(IL, IR, 2) ? 4 : 2;
+    return from_dwords(L, X, IL, IR, I1) ? 3 : 2;
+  }
   return fast ? 1 : 0;
 }
 

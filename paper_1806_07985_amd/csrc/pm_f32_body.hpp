@@ -43,8 +43,8 @@ namespace pm32 {
 // loads in flight once per ring round; it serves ragged tensors whose matricisation
 // has columns of 34 MB and more on the right (67 at R > 32) or 143 MB on the left.
 // The streaming (nontemporal) hint goes with LD_FAST and LD_BUFNT on the left,
-// where a tensor's columns start on cache lines: every line is then read once, by
-// one load (128^4 left node 0.18 ms with the hint, 0.20 without; 1024^3 0.69 and
+// where a tensor's columns start on cache lines (and for the largest tensors,
+// pm_left_stream): every line is then read once, by one load (128^4 left node 0.18 ms with the hint, 0.20 without; 1024^3 0.69 and
 // 0.79). Everywhere else a line is read by two loads, of neighbouring rows or
 // steps, or by a step's two halves on the right, and the hint drops it in between:
 // right node of 1000x999x300 R = 20 401 -> 276 us without it, of 1024^3 R = 32

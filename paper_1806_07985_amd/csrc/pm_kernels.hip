@@ -378,19 +378,19 @@ bool pm_f32_buf(int side, int64_t IL, int nb) {
 // with the streaming hint on the left if columns start on cache lines: against the
 // masked ones, left node of 1000x999x300 R = 20 0.288 -> 0.245 ms, of 137x201x90
 // R = 16 29.8 -> 23.3 us; against the plain ones, left node of 1024^3 0.79 -> 0.69
-// ms, 512^3 R = 10 equal. Left nodes with columns of 16 KB and more keep the plain
+// ms, 512^3 R = 10 equal; and for the largest tensors (pm_left_stream). Left nodes with columns of 16 KB and more keep the plain
 // loads where the shape allows them: 64^5 (16 KB) takes 1.72 ms per iteration with
 // them and 1.78 range-checked, 128^4 (64 KB) 0.438 and 0.457.
-int pm_f32_load_form(const PmLaunch& L, int64_t IL, int I1) {
+int pm_f32_load_form(const PmLaunch& L, int64_t IL, int64_t IR, int I1) {
   const bool fast = pm_f32_fast(L.side, IL, I1, L.nb, L.xs), lines = L.side == 0 && IL % 32 == 0;
   if (fast && lines && IL >= 4096) return LD_FAST;
-  if (pm_f32_buf(L.side, IL, L.nb)) return lines ? LD_BUFNT : LD_BUF;
+  if (pm_f32_buf(L.side, IL, L.nb)) return lines || (L.side == 0 && pm_left_stream(IL, IR, 4)) ? LD_BUFNT : LD_BUF;
   return fast ? LD_FAST : LD_GEN;
 }
 
 hipError_t pm_launch_f32(const PmLaunch& L, const PmArgs& a, const Sink& sk) {
   const int wm = a.wm;
-  const int ld = pm_f32_load_form(L, a.IL, a.I1);
+  const int ld = pm_f32_load_form(L, a.IL, a.IR, a.I1);
   const bool mt = L.mper > 1;
   // variant = xs*100000 + wide*10000 + side*1000 + nb*100 + mt*10 + ld (wide: launched with more LDS)
   const int variant =

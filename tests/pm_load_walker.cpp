@@ -222,11 +222,13 @@ int main() {
       if (L.xs) continue;  // its loads are walked by pm_address_emulator.cpp
       Case c{dt == NNCP_F32, side, 0, xoff, IL, IR, (int64_t)IL * IR};
       const void* X = (const void*)(((uintptr_t)1 << 40) + xoff * (dt == NNCP_F32 ? 4 : 2));
-      c.ld = c.f32 ? pm_f32_load_form(L, IL, I1) : pm16_load_form(L, X, IL, IR, I1);
+      c.ld = c.f32 ? pm_f32_load_form(L, IL, IR, I1) : pm16_load_form(L, X, IL, IR, I1);
       const long long was = bad;
+      const int form = c.ld;
+      if (!c.f32 && c.ld == 4) c.ld = BUF;  // (the streaming hint changes no address)
       if (side) right(c, L);
       else left(c, L);
-      printf("cover %s side %d form %d mt %d split %d j1 %d stages %d wm %d nb %d%s\n", c.f32 ? "f32" : "16", side, c.ld, L.mper > 1,
+      printf("cover %s side %d form %d mt %d split %d j1 %d stages %d wm %d nb %d%s\n", c.f32 ? "f32" : "16", side, form, L.mper > 1,
              L.nsplit > 1, L.j1, L.istages > 1, L.wm, L.nb, bad > was ? " FAIL" : "");
       if (bad > was) printf("  ^ dtype %d IL %lld IR %lld I1 %d R %d offset %d\n", dt, IL, IR, I1, R, xoff);
     }

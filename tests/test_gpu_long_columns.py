@@ -70,3 +70,28 @@ def test_split_sums_of_every_length(gpu_lib, t, R):
     """About t splits over K: the sum's runs of sixteen, of four and its rest."""
     _check((16, 64 * t, 7), 2, 1, R, "f32", 0.5)
     _check((16, 64 * t, 7), 2, 1, R, "bf16", 0.5)
+
+
+@pytest.mark.parametrize("dims,dt", [((30013, 1200, 84), "f32"), ((30012, 1200, 168), "bf16"), ((30012, 1200, 168), "f16")])
+@pytest.mark.parametrize("R", [10, 20, 33])
+def test_left_nodes_of_tensors_past_12_gb(gpu_lib, dims, dt, R):
+    """A left node that is streamed (12.1 GB) against the sum of its two halves along
+    the last mode, which are not: exact integers, so the sums are equal."""
+    import torch
+    from paper_1806_07985_amd import native
+    print(f"case past 12 GB {dt} dims={dims} R={R}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(R)
+    n, half = int(np.prod(dims)), int(np.prod(dims)) // 2
+    X = torch.empty(n, device="cuda", dtype={"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dt])
+    for i in range(0, n, 1 << 29):
+        part = X[i:i + (1 << 29)]
+        part.copy_(torch.rand(part.numel(), device="cuda", generator=g) < 0.02)
+    X[-1] = 3
+    H = [torch.randint(0, 3, (R, d), device="cuda", generator=g).float() for d in dims]
+    k = dims[2] // 2
+    T = native.partial_mttkrp(X, list(dims), 1, 0, H, R)
+    a = native.partial_mttkrp(X[:half], [dims[0], dims[1], k], 1, 0, [H[0], H[1], H[2][:, :k].contiguous()], R)
+    b = native.partial_mttkrp(X[half:], [dims[0], dims[1], k], 1, 0, [H[0], H[1], H[2][:, k:].contiguous()], R)
+    assert float(T.max()) < 2 ** 24 and float(T.max()) > 0
+    assert torch.equal(T, a + b)

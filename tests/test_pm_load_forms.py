@@ -73,3 +73,11 @@ def test_right_nodes_load_from_dword_starts_where_that_is_faster(walk, d, R, for
     for off, f in ((0, form), (1, 2)):
         seen = walk(None, None, [f"2 {d[0] * d[1]} {d[2]} {d[2]} {d[0]} {R} {off}"])
         assert any(s.startswith(f"16 side 1 form {f}") for s in seen), (off, sorted(seen))
+
+
+@pytest.mark.parametrize("d,dt,form", [((30013, 1200, 83), 0, 2), ((30013, 1200, 84), 0, 3), ((255, 3000, 30000), 0, 2), ((257, 3000, 30000), 0, 3),
+                                       ((30012, 1200, 166), 1, 2), ((30012, 1200, 167), 2, 4), ((511, 3000, 30000), 1, 2), ((513, 3000, 30000), 1, 4)])
+def test_left_nodes_of_large_tensors_stream(walk, d, dt, form):
+    """From 12 GB with columns of 1 KB and more (split 1)."""
+    seen = walk(None, None, [f"{dt} {d[0]} {d[1] * d[2]} {d[1]} {d[0]} 10 0"])
+    assert any(s.startswith(f"{'16' if dt else 'f32'} side 0 form {form} ") for s in seen), sorted(seen)
