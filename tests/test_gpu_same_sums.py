@@ -10,7 +10,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dims,R,kw", [((60, 50, 40), 5, {}), ((33, 21, 10, 9), 40, {"update": "mu"}),
                                        ((6, 5, 1100), 4, {"split": 1}), ((57, 31, 20), 72, {}),
-                                       ((30, 20, 25), 8, {"no_tree": True}), ((24, 20, 17), 8, {"inner_sweeps": 7})])
+                                       ((30, 20, 25), 8, {"no_tree": True}), ((24, 20, 17), 8, {"inner_sweeps": 7}),
+                                       ((4, 3, 60001), 20, {"split": 2}),  # more than 32 row chunks
+                                       ((9301, 8, 5), 10, {"inner_sweeps": 7, "split": 1}),  # either side of the update's line
+                                       ((16, 640, 7), 5, {"split": 2, "pm_wg_kib": 4})])  # sums over many splits
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_same_bits_by_every_route(gpu_lib, dims, R, kw, dt):
     import torch
